@@ -80,8 +80,8 @@ typedef struct igks_options {
     int chunk;          /* iterations per captured HIP graph launch; 0 = no graph */
     int block;          /* threads per block of the cell/face kernels; 0 = 256 */
     int sweep;          /* LU-SGS sweep schedule: 0 auto, 1 one launch per wavefront,
-                           2 all wavefronts in one workgroup (barrier between wavefronts),
-                           3 one wave per sweep block (igks_set_sweep_blocks), all blocks at once */
+                           2 or 3 one workgroup per instance or, with igks_set_sweep_blocks, per
+                           sweep block, all of them at once */
     int flux_lanes;     /* lanes per face of the flux kernel: 0 auto (2 below 32768 faces),
                            1 or 2; the two agree to rounding */
     int scheme;         /* 0: implicit LU-SGS (Eq.18-22); 1: explicit Eq.15 with local time
@@ -105,7 +105,7 @@ typedef struct igks_options {
                            2: a second pass solves the same block system again with the cross-block
                            terms of the first pass's increments moved to its right-hand side (one
                            block-Jacobi correction of the coupling the blocks leave out; not in the
-                           paper).  Two passes run on the wave-per-block schedule (sweep 0 or 3;
+                           paper).  Two passes run on the workgroup-per-block schedule (sweep 0 or 3;
                            1 or 2 with block_passes 2 is IGKS_EINVAL) and take a second increment
                            array in the workspace. */
     int lusgs_op;       /* dissipation of the LU-SGS operator (Eq.18-22): 0 (default) the scalar
@@ -148,8 +148,8 @@ typedef struct igks_ctx igks_ctx;
 
 /* Fill *opt with the defaults: FP64, limiter off, cfl_init 1000 (Sec. 3.1),
  * cfl_min 1, cfl_max 1e6, Eq.25 law, cfl_flux 1, visc_sr on, Sutherland,
- * chunk 20, block 256, sweep auto (a wave per sweep block when an instance has
- * sweep blocks, else one workgroup when the wavefronts are many and narrow:
+ * chunk 20, block 256, sweep auto (a workgroup per sweep block when an instance has
+ * sweep blocks, else one per instance when the wavefronts are many and narrow:
  * more than 16 of them averaging under 1024 cells), flux_lanes auto. */
 void igks_default_options(igks_options *opt);
 
@@ -323,15 +323,15 @@ int igks_batch_status(igks_ctx *ctx, int32_t inst, int32_t *halted);
 /* Autotuner: runs `iters` iterations under each candidate launch schedule
  * (threads per block 64/128/256 for the prep, flux, gather and sweep
  * kernels, the face flux on one or two lanes per face; for the sweeps also
- * one workgroup for all wavefronts, tried while wavefronts average under
- * 16384 cells, and a wave per sweep block when there are sweep blocks),
+ * one workgroup per instance, tried while wavefronts average under
+ * 16384 cells, and a workgroup per sweep block when there are sweep blocks),
  * keeps the fastest per kernel class, and then restores both
  * state buffers, the scalars and the history bitwise.  Block sizes and the
  * sweep schedule never change results; the one- and two-lane flux kernels
  * agree to rounding (the compiler fuses a few multiply-adds differently).
  * schedule6 (may be NULL) receives the
  * block sizes of the four classes, the sweep schedule (1: one launch per
- * wavefront, 2: one workgroup, 3: a wave per sweep block) and the lanes per
+ * wavefront, 2 or 3: a workgroup per instance or sweep block) and the lanes per
  * face of the flux (1 or 2;
  * before any tuning 2 below 32768 faces).  IGKS_EINVAL unless
  * 1 <= iters <= 1000; IGKS_ENONPHYS if an instance is frozen. */

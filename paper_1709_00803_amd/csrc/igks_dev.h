@@ -94,7 +94,7 @@ struct Params {
                                // diagonal block, entry (r, k) at (4 r + k) nc + c; null with
                                // the scalar operator
     int roe_kin;               // Roe-matrix operator with the kinetic wave magnitudes
-    const double *xc, *yc, *area, *lsinv, *dwall;
+    const double *area, *lsinv, *dwall;
     const double *vtx;         // vertex offsets from the centroid: (x, y) of slot v of block b at (2v) nb + b
     int nb;                    // entry / vertex blocks: nc + overflow blocks
     // cell-face entries, MAXV per block (entry MAXV b + k; block b = c, then
@@ -123,8 +123,8 @@ struct Params {
     // array puts sixteen faces in a cache line where the records put two
     double *flam, *fsak;
     // per-instance cell lists (internal ids, ascending) for the norms
-    const int *icell, *ioff;
-    const int *ipos;           // position of each cell in icell
+    const int *ioff;
+    const int *ipos;           // position of each cell in its instance's list
     // processing order of the cell kernels k_prep and k_gather: cells grouped
     // in spatial tiles, each tile's wavefronts one after another, so that a
     // cell and its neighbours (which lie in other wavefronts) are read by the
@@ -156,14 +156,22 @@ template <typename T> void launch_roe_diag(const Launch &L, const Params<T> &P);
 // is not launched (its increments are formed where they are read); 0: every
 // forward increment is stored.
 template <typename T> void launch_sweep(const Launch &L, const Params<T> &P, int c0, int c1, int mode, int lev1);
-template <typename T> void launch_sweep_wg(const Launch &L, const Params<T> &P, const int *lev_off, int nlev, bool fwd);
-// the whole sweep, one wave per sweep block (ngb blocks; block gb's k-th
-// wavefront = cells [bl_lo[bl_off[gb] + k], bl_hi[bl_off[gb] + k])); the
-// backward sweep is followed by the update of every cell unless `update` is
-// false (the first of two block passes)
+// Groups of cells that the sweeps do not couple (sweep blocks; an instance
+// without blocks is one), each swept by one workgroup.
+constexpr int CHUNK_CELLS = 16;
+struct SweepGroups {
+    int n;                              // groups
+    int slots, waves;                   // LDS slots, waves per group
+    const int *cslot;                   // LDS slot of each cell, -1: the group's increments stay in global memory
+    const int *ch_off;                  // group g's chunks: [ch_off[g], ch_off[g + 1])
+    const int4 *chunk;                  // c0, c1, chunks of earlier (forward) and of later wavefronts
+};
+// LDS of a group's ring and its count of finished chunks
+constexpr size_t grp_lds(int slots, size_t size) { return 5 * size * (size_t)slots + 16; }
+// the whole forward or backward sweep, one launch; `update`: followed by the
+// update of every cell (after the last backward sweep)
 template <typename T>
-void launch_sweep_blk(const Launch &L, const Params<T> &P, const int *bl_off, const int *bl_lo, const int *bl_hi,
-                      int ngb, bool fwd, bool update = true);
+void launch_sweep_grp(const Launch &L, const Params<T> &P, const SweepGroups &G, bool fwd, bool update);
 template <typename T> void launch_commit(const Launch &L, const Params<T> &P, int it);
 // explicit step (Eq.15, local time steps) in place of the sweeps
 template <typename T> void launch_explicit(const Launch &L, const Params<T> &P);

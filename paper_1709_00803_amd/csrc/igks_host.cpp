@@ -46,10 +46,14 @@ struct Global {
     int N = 0, F = 0, nlev = 0, nwall = 0, max_inst_cells = 0;
     int NB = 0;                      // entry / vertex blocks: N + one overflow block per polygon
     std::vector<int> lev_off;        // wavefront offsets (internal cells)
-    // sweep blocks of all instances (an instance without blocks is one):
-    // block gb's cells of its k-th wavefront are the internal cells
-    // [bl_lo[bl_off[gb] + k], bl_hi[bl_off[gb] + k])
-    std::vector<int> bl_off, bl_lo, bl_hi;
+    // groups the sweeps do not couple: the sweep blocks of all instances (an
+    // instance without blocks is one).  Group g's chunks of at most
+    // CHUNK_CELLS cells of one wavefront, in forward order, are
+    // chunk[ch_off[g]] .. chunk[ch_off[g + 1] - 1]; cslot: a cell's slot in the
+    // ring of increments its group's sweep keeps in LDS
+    std::vector<int> ch_off, cslot;
+    std::vector<int4> chunk;
+    int grp_slots = 0, grp_waves = 4;
     std::vector<int> coff;           // first global upload id of each instance
     std::vector<int> g2i;            // global upload id -> internal cell
     std::vector<int> cinst, finst, icell, ioff, ipos, cperm;
@@ -71,11 +75,11 @@ struct Buf {
 constexpr int NKT = 6;
 
 struct WsMap {
-    Buf ip, is, slot, Wa, Wb, grad, lamc, vort, nu, M, lsum, sadiag, r2, dW, dW1, dinv, xc, yc, area, lsinv, dwall, vtx, phi;
-    Buf cinst, finst, icell, ioff, g2i, cf_face, cf_nbr, cf_flag, cf_dx, cf_dy;
+    Buf ip, is, slot, Wa, Wb, grad, lamc, vort, nu, M, lsum, sadiag, r2, dW, dW1, dinv, area, lsinv, dwall, vtx, phi;
+    Buf cinst, finst, ioff, g2i, cf_face, cf_nbr, cf_flag, cf_dx, cf_dy;
     Buf fl, fr, fbc, fnx, fny, flen, frl, frr, fidl, fidr, firn, ipart, hist, ipos, cperm;
     Buf frec, flam, fsak, enx, eny, es;
-    Buf wall_faces, wall_out, woff, wseg, lev_off, bl_off, bl_lo, bl_hi, stage, backup;
+    Buf wall_faces, wall_out, woff, wseg, ch_off, cslot, chunk, stage, backup;
     size_t total;
 };
 
@@ -101,7 +105,7 @@ struct igks_ctx {
     int hist_cap = 0;
     // launch schedule
     int block[NCLASS] = {256, 256, 256, 256};
-    int sweep_mode = 1;       // LU-SGS sweeps: 1 a launch per wavefront, 2 one workgroup, 3 a wave per sweep block
+    int sweep_mode = 1;       // LU-SGS sweeps: 1 a launch per wavefront, 2 or 3 a workgroup per instance / sweep block
     bool flux_pair = false;   // face flux on two lanes per face
     // host copies of the device scalars and the history of the last iterate call
     std::vector<InstScalars> hs;
@@ -176,16 +180,15 @@ int graph_chunk_for(const igks_ctx *c, int sweep_mode)
 }
 int graph_chunk(const igks_ctx *c) { return graph_chunk_for(c, c->sweep_mode); }
 
-// The schedule chosen at binding time from the sizes: one workgroup for the
-// sweeps when wavefronts are many and narrow (one workgroup of 512 threads
-// takes a wavefront per round of 512 cells and a launch per wavefront costs
-// a few microseconds, so the workgroup wins up to about two rounds); one
-// lane per face (its kernel holds two waves per SIMD and executes the
-// fewest instructions per face) except on small meshes, where two lanes
+// The schedule chosen at binding time from the sizes: one workgroup per
+// instance for the sweeps when wavefronts are many and narrow (a workgroup
+// takes 0.4 to 1 us a wavefront of up to a hundred cells, a launch 4 us or
+// more); one lane per face (its kernel holds two waves per SIMD and executes
+// the fewest instructions per face) except on small meshes, where two lanes
 // per face give the SIMDs twice as many waves to switch between.
 //
 // With sweep blocks the cells of different blocks never wait for each other,
-// so one wave sweeps each block on its own (no launch per wavefront, no
+// so one workgroup sweeps each block on its own (no launch per wavefront, no
 // barrier across blocks).
 bool any_sweep_blocks(const igks_ctx *c)
 {
@@ -359,9 +362,6 @@ int build_instance(igks_ctx *ctx, int n_nodes, const double *xy, int n_cells, co
     return IGKS_OK;
 }
 
-// Concatenate the instances in the internal order: cells by (wavefront,
-// instance, upload index); interior faces by internal owner, then boundary
-// faces by internal owner.
 // Processing order of the cell kernels (Global::cperm): per instance, its
 // cells ranked along a Morton curve of their centroids and cut into tiles
 // of TILE_CELLS; each tile's cells by wavefront, then internal index.  In a
@@ -413,6 +413,95 @@ void cell_tiles(Global &G, int ni)
     }
 }
 
+// LDS of one sweep group's ring of increments, at most: the CU has 160 KB,
+// shared by the groups that run on it at once (256 CUs); below 48 KB the
+// waves of three groups fill a CU's registers anyway.
+size_t ring_bytes_max(int ngroups)
+{
+    const size_t per_cu = (size_t)std::max(1, (ngroups + 255) / 256);
+    return std::min<size_t>(152 << 10, std::max<size_t>(48 << 10, (160 << 10) / per_cu));
+}
+
+// Groups, chunks and LDS slots of the group sweep (Global::chunk).  A cell's
+// rank is its place in its group's sweep order (wavefront, then internal
+// index).  A slot may be used again once no cell that still has to run
+// needs its increment: those cells lie in the wavefront being swept or
+// beyond, so a ring holds if it has at least as many slots as the largest
+// rank distance between two coupled cells plus the widest wavefront (or as
+// the group has cells).
+void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vector<int> &glev,
+                  const std::vector<int> &gblk, int ngb)
+{
+    Global &G = ctx->g;
+    const int N = G.N, ni = (int)ctx->inst.size();
+    // per group, its wavefronts in order: each a contiguous range of internal
+    // cells (the internal order is by wavefront, then group)
+    std::vector<std::vector<std::pair<int, int>>> rng(ngb);
+    std::vector<int> rank(N), cells(ngb, 0), width(ngb, 0), span(ngb, 0);
+    for (int c = 0; c < N; c++) {
+        const int b = gblk[order[c]];
+        auto &r = rng[b];
+        if ((int)r.size() == glev[order[c]]) r.push_back({c, c + 1});
+        else r.back().second = c + 1;   // cells of one group and wavefront are adjacent
+        rank[c] = cells[b]++;
+        width[b] = std::max(width[b], r.back().second - r.back().first);
+    }
+    for (int i = 0; i < ni; i++) {
+        const InstMesh &m = ctx->inst[i];
+        for (const auto &f : m.uf) {
+            if (f.r < 0 || !same_block(m, f.l, f.r)) continue;
+            const int a = G.g2i[G.coff[i] + f.l], b = G.g2i[G.coff[i] + f.r], g = gblk[G.coff[i] + f.l];
+            span[g] = std::max(span[g], std::abs(rank[a] - rank[b]));
+        }
+    }
+    const size_t cap = ring_bytes_max(ngb), size = ctx->opt.precision == IGKS_MIXED ? sizeof(float) : sizeof(double);
+    std::vector<int> need(ngb);
+    G.grp_slots = 1;
+    for (int b = 0; b < ngb; b++) {
+        need[b] = std::max(1, std::min(cells[b], span[b] + width[b]));
+        if (grp_lds(need[b], size) <= cap) G.grp_slots = std::max(G.grp_slots, need[b]);
+        else need[b] = 0;
+    }
+    G.cslot.resize(N);
+    for (int c = 0; c < N; c++) {
+        const int b = gblk[order[c]];
+        G.cslot[c] = need[b] > 0 ? rank[c] % G.grp_slots : -1;
+    }
+    G.ch_off.assign(ngb + 1, 0);
+    G.chunk.clear();
+    size_t nfronts = 0;
+    for (int b = 0; b < ngb; b++) {
+        const size_t k0 = G.chunk.size();
+        for (auto &p : rng[b]) {
+            const int before = (int)(G.chunk.size() - k0);
+            for (int c0 = p.first; c0 < p.second; c0 += CHUNK_CELLS)
+                G.chunk.push_back(make_int4(c0, std::min(c0 + CHUNK_CELLS, p.second), before, 0));
+        }
+        for (size_t k = G.chunk.size(), later = 0; k > k0;) {
+            // chunks of the wavefront that ends at k, all with the same count of later ones
+            size_t f = k;
+            while (f > k0 && G.chunk[f - 1].z == G.chunk[k - 1].z) f--;
+            for (size_t x = f; x < k; x++) G.chunk[x].w = (int)later;
+            later += k - f;
+            k = f;
+        }
+        nfronts += rng[b].size();
+        G.ch_off[b + 1] = (int)G.chunk.size();
+    }
+    // Four waves, one per SIMD, take turns where a wavefront is mostly one
+    // chunk or where the groups fill the CUs; where few groups have wider
+    // wavefronts, eight run their chunks at once.  Forward + backward sweep in
+    // us with 4 / 8 waves: 64x32 plate, 21 blocks 38 / 38; 250k aerofoil, 523
+    // blocks of 1.8 chunks a wavefront, 254 / 260; 350k plate, 1367 blocks,
+    // 771 / 1189; in natural order the plate 132 / 110, the 100x100 cavity
+    // (3.6 chunks a wavefront) 522 / 364.
+    const double per_front = (double)G.chunk.size() / std::max<size_t>(1, nfronts);
+    G.grp_waves = per_front > 1.35 && ngb <= 256 ? 8 : 4;
+}
+
+// Concatenate the instances in the internal order: cells by (wavefront,
+// instance, upload index); interior faces by internal owner, then boundary
+// faces by internal owner.
 int combine(igks_ctx *ctx)
 {
     Global &G = ctx->g;
@@ -448,23 +537,7 @@ int combine(igks_ctx *ctx)
     G.lev_off.assign(G.nlev + 1, 0);
     for (int c = 0; c < N; c++) G.lev_off[glev[order[c]] + 1]++;
     for (int l = 0; l < G.nlev; l++) G.lev_off[l + 1] += G.lev_off[l];
-    {
-        // per sweep block, its wavefronts in order: each a contiguous range of
-        // internal cells (the internal order is by wavefront, then block)
-        std::vector<std::vector<std::pair<int, int>>> rng(ngb);
-        for (int c = 0; c < N; c++) {
-            auto &r = rng[gblk[order[c]]];
-            const int lv = glev[order[c]];
-            if ((int)r.size() == lv) r.push_back({c, c + 1});
-            else r.back().second = c + 1;   // cells of one block and wavefront are adjacent
-        }
-        G.bl_off.assign(ngb + 1, 0);
-        G.bl_lo.clear(); G.bl_hi.clear();
-        for (int b = 0; b < ngb; b++) {
-            for (auto &p : rng[b]) { G.bl_lo.push_back(p.first); G.bl_hi.push_back(p.second); }
-            G.bl_off[b + 1] = (int)G.bl_lo.size();
-        }
-    }
+    sweep_groups(ctx, order, glev, gblk, ngb);
     G.cinst.resize(N);
     for (int c = 0; c < N; c++) G.cinst[c] = gi[order[c]];
     G.ioff.assign(ni + 1, 0);
@@ -664,9 +737,9 @@ WsMap layout(const Global &G, int ninst, const igks_options &o, int hist_cap)
     w.dW1 = L.add(o.block_passes == 2 ? 5 * N * (o.precision == IGKS_MIXED ? sizeof(float) : D) : 0);
     // the inverted 4x4 LU-SGS diagonal blocks (Roe-matrix operator)
     w.dinv = L.add(o.lusgs_op >= 1 && o.scheme == 0 ? 16 * N * (o.precision == IGKS_MIXED ? sizeof(float) : D) : 0);
-    w.xc = L.add(N * D); w.yc = L.add(N * D); w.area = L.add(N * D); w.lsinv = L.add(3 * N * D);
+    w.area = L.add(N * D); w.lsinv = L.add(3 * N * D);
     w.dwall = L.add(N * D); w.vtx = L.add(2 * MAXV * (size_t)G.NB * D);
-    w.cinst = L.add(N * I); w.finst = L.add(F * I); w.icell = L.add(N * I); w.ioff = L.add((NI + 1) * I);
+    w.cinst = L.add(N * I); w.finst = L.add(F * I); w.ioff = L.add((NI + 1) * I);
     w.g2i = L.add(N * I);
     w.cf_face = L.add(E * I); w.cf_nbr = L.add(E * I); w.cf_flag = L.add(E * I);
     w.cf_dx = L.add(E * D); w.cf_dy = L.add(E * D);
@@ -683,10 +756,9 @@ WsMap layout(const Global &G, int ninst, const igks_options &o, int hist_cap)
     w.wall_out = L.add(4 * NW * D);
     w.woff = L.add((NI + 1) * I);
     w.wseg = L.add(4 * NW * D);
-    w.lev_off = L.add((size_t)(G.nlev + 1) * I);
-    w.bl_off = L.add(G.bl_off.size() * I);
-    w.bl_lo = L.add(std::max<size_t>(1, G.bl_lo.size()) * I);
-    w.bl_hi = L.add(std::max<size_t>(1, G.bl_hi.size()) * I);
+    w.ch_off = L.add(G.ch_off.size() * I);
+    w.cslot = L.add(N * I);
+    w.chunk = L.add(G.chunk.size() * sizeof(int4));
     w.stage = L.add(5 * (size_t)std::max(1, G.max_inst_cells) * D);
     w.backup = L.add(10 * N * D + NI * sizeof(InstScalars));
     w.total = L.total;
@@ -717,7 +789,7 @@ void fill_params(igks_ctx *c, Params<T> &P)
     P.dWx = nullptr;
     P.dinv = c->opt.lusgs_op >= 1 && c->opt.scheme == 0 ? (T *)(b + w.dinv.off) : nullptr;
     P.roe_kin = c->opt.lusgs_op == 2;
-    P.xc = D(w.xc); P.yc = D(w.yc); P.area = D(w.area); P.lsinv = D(w.lsinv); P.dwall = D(w.dwall); P.vtx = D(w.vtx);
+    P.area = D(w.area); P.lsinv = D(w.lsinv); P.dwall = D(w.dwall); P.vtx = D(w.vtx);
     P.nb = c->g.NB;
     P.cf_face = In(w.cf_face); P.cf_nbr = In(w.cf_nbr); P.cf_flag = In(w.cf_flag);
     P.cf_dx = D(w.cf_dx); P.cf_dy = D(w.cf_dy);
@@ -726,7 +798,7 @@ void fill_params(igks_ctx *c, Params<T> &P)
     P.fidl = D(w.fidl); P.fidr = D(w.fidr); P.firn = D(w.firn);
     P.frec = D(w.frec); P.flam = D(w.flam); P.fsak = D(w.fsak);
     P.enx = D(w.enx); P.eny = D(w.eny); P.es = D(w.es);
-    P.icell = In(w.icell); P.ioff = In(w.ioff); P.ipos = In(w.ipos); P.cperm = In(w.cperm); P.ipart = D(w.ipart); P.rb = norm_rb(c->g);
+    P.ioff = In(w.ioff); P.ipos = In(w.ipos); P.cperm = In(w.cperm); P.ipart = D(w.ipart); P.rb = norm_rb(c->g);
     P.hist = D(w.hist); P.hist_cap = c->hist_cap;
 }
 
@@ -739,12 +811,23 @@ Launch launch_of(igks_ctx *c)
     return L;
 }
 
+SweepGroups groups_of(igks_ctx *c)
+{
+    SweepGroups S;
+    S.n = (int)c->g.ch_off.size() - 1;
+    S.slots = c->g.grp_slots;
+    S.waves = c->g.grp_waves;
+    S.ch_off = (const int *)(c->ws + c->w.ch_off.off);
+    S.cslot = (const int *)(c->ws + c->w.cslot.off);
+    S.chunk = (const int4 *)(c->ws + c->w.chunk.off);
+    return S;
+}
+
 // queue one nonlinear iteration of every instance
 template <typename T>
 void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it)
 {
     Launch L = launch_of(c);
-    const int *lev = (const int *)(c->ws + c->w.lev_off.off);
     const Global &G = c->g;
     const int lev1 = G.nlev > 1 ? G.lev_off[1] : 0;   // cells of the first wavefront
     auto mark = [&](int k) { if (ev) (void)hipEventRecord(ev[k], c->stream); };
@@ -768,9 +851,7 @@ void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it)
     // Roe-matrix operator: the inverted diagonal blocks, which need the CFL
     // number the reduction has just set (timed with the forward sweep)
     if (P.dinv) launch_roe_diag(L, P);
-    const int *blo = (const int *)(c->ws + c->w.bl_off.off), *bll = (const int *)(c->ws + c->w.bl_lo.off),
-              *blh = (const int *)(c->ws + c->w.bl_hi.off);
-    const int ngb = (int)G.bl_off.size() - 1;
+    const SweepGroups S = groups_of(c);
     if (c->sweep_mode == 3 && two_block_passes(c)) {
         // a first block pass into the second increment array, then the
         // second pass with its cross-block terms (the forward class holds
@@ -778,13 +859,12 @@ void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it)
         Params<T> P1 = P;
         P1.dW = (T *)(c->ws + c->w.dW1.off);
         P1.dWx = nullptr;
-        launch_sweep_blk(L, P1, blo, bll, blh, ngb, true);
-        launch_sweep_blk(L, P1, blo, bll, blh, ngb, false, false);
+        launch_sweep_grp(L, P1, S, true, false);
+        launch_sweep_grp(L, P1, S, false, false);
         Params<T> P2 = P;
         P2.dWx = P1.dW;
-        launch_sweep_blk(L, P2, blo, bll, blh, ngb, true);
-    } else if (c->sweep_mode == 3) launch_sweep_blk(L, P, blo, bll, blh, ngb, true);
-    else if (c->sweep_mode == 2) launch_sweep_wg(L, P, lev, G.nlev, true);
+        launch_sweep_grp(L, P2, S, true, false);
+    } else if (c->sweep_mode >= 2) launch_sweep_grp(L, P, S, true, false);
     else
         // forward over the wavefronts after the first (whose forward
         // increments D^-1 M are formed where they are read); the last one
@@ -793,8 +873,7 @@ void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it)
             launch_sweep(L, P, G.lev_off[l], G.lev_off[l + 1], l + 1 < G.nlev ? 0 : 2, lev1);
     mark(5);
     // backward sweep with the update
-    if (c->sweep_mode == 3) launch_sweep_blk(L, P, blo, bll, blh, ngb, false);
-    else if (c->sweep_mode == 2) launch_sweep_wg(L, P, lev, G.nlev, false);
+    if (c->sweep_mode >= 2) launch_sweep_grp(L, P, S, false, true);
     else
         for (int l = G.nlev - 2; l >= 0; l--) launch_sweep(L, P, G.lev_off[l], G.lev_off[l + 1], 1, lev1);
     mark(6);   // the backward sweeps' class ends here; the commit belongs to no class
@@ -1243,10 +1322,10 @@ int igks_bind_workspace(igks_ctx *c, void *dptr, size_t bytes)
     };
     const size_t D = sizeof(double), I = sizeof(int), N = G.N, F = G.F, E = (size_t)MAXV * G.NB;
     rc = 0;
-    rc |= up(w.xc, G.xc.data(), N * D); rc |= up(w.yc, G.yc.data(), N * D); rc |= up(w.area, G.area.data(), N * D);
+    rc |= up(w.area, G.area.data(), N * D);
     rc |= up(w.lsinv, G.lsinv.data(), 3 * N * D); rc |= up(w.vtx, G.vtx.data(), G.vtx.size() * D);
     rc |= up(w.cinst, G.cinst.data(), N * I); rc |= up(w.finst, G.finst.data(), F * I);
-    rc |= up(w.icell, G.icell.data(), N * I); rc |= up(w.ioff, G.ioff.data(), G.ioff.size() * I);
+    rc |= up(w.ioff, G.ioff.data(), G.ioff.size() * I);
     rc |= up(w.ipos, G.ipos.data(), N * I);
     rc |= up(w.cperm, G.cperm.data(), N * I);
     rc |= up(w.g2i, G.g2i.data(), N * I);
@@ -1266,10 +1345,12 @@ int igks_bind_workspace(igks_ctx *c, void *dptr, size_t bytes)
     rc |= up(w.wall_faces, G.wall_faces.data(), G.wall_faces.size() * I);
     rc |= up(w.woff, G.woff.data(), G.woff.size() * I);
     rc |= up(w.wseg, G.wseg.data(), G.wseg.size() * D);
-    rc |= up(w.lev_off, G.lev_off.data(), G.lev_off.size() * I);
-    rc |= up(w.bl_off, G.bl_off.data(), G.bl_off.size() * I);
-    rc |= up(w.bl_lo, G.bl_lo.data(), G.bl_lo.size() * I);
-    rc |= up(w.bl_hi, G.bl_hi.data(), G.bl_hi.size() * I);
+    rc |= up(w.ch_off, G.ch_off.data(), G.ch_off.size() * I);
+    rc |= up(w.cslot, G.cslot.data(), N * I);
+    rc |= up(w.chunk, G.chunk.data(), G.chunk.size() * sizeof(int4));
+    // centroids for the wall distance, in the autotuner's backup area
+    const Buf cx{w.backup.off, N * D}, cy{w.backup.off + N * D, N * D};
+    rc |= up(cx, G.xc.data(), N * D); rc |= up(cy, G.yc.data(), N * D);
     if (rc) return rc;
     c->sweep_mode = auto_sweep_mode(c);
     c->flux_pair = auto_flux_pair(c);
@@ -1280,7 +1361,7 @@ int igks_bind_workspace(igks_ctx *c, void *dptr, size_t bytes)
     rc = up(w.ip, ip0.data(), sizeof(InstParam) * ip0.size());
     if (rc) return rc;
     Launch L = launch_of(c);
-    launch_wall_distance(L, G.N, c->P64.xc, c->P64.yc, c->P64.cinst, (const int *)(b + w.woff.off),
+    launch_wall_distance(L, G.N, (const double *)(b + cx.off), (const double *)(b + cy.off), c->P64.cinst, (const int *)(b + w.woff.off),
                          (const double *)(b + w.wseg.off), (double *)(b + w.dwall.off));
     launch_reset(L, c->P64, 15, -1);
     HIPCHK(c, hipGetLastError());
@@ -1590,7 +1671,7 @@ int igks_set_schedule(igks_ctx *c, const int32_t *s6)
     if (s6[NCLASS] < 1 || s6[NCLASS] > 3 || (s6[NCLASS + 1] != 1 && s6[NCLASS + 1] != 2))
         return fail(c, IGKS_EINVAL, "the sweep schedule must be 1, 2 or 3 and the lanes per face 1 or 2");
     if (two_block_passes(c) && s6[NCLASS] != 3)
-        return fail(c, IGKS_EINVAL, "two block passes run on the wave-per-block sweep schedule (3)");
+        return fail(c, IGKS_EINVAL, "two block passes run on the workgroup-per-block sweep schedule (3)");
     destroy_graph(c);
     for (int k = 0; k < NCLASS; k++) c->block[k] = s6[k];
     c->sweep_mode = s6[NCLASS];
@@ -1653,10 +1734,9 @@ int igks_autotune(igks_ctx *c, int32_t iters, int32_t *s6)
         }
     for (int k = 0; k < NCLASS; k++) c->block[k] = best[k];
     c->flux_pair = rc ? pair_auto : best_pair;
-    // sweeps: one launch per wavefront (timed above), one workgroup (a
-    // candidate only while wavefronts are narrow), a wave per sweep block
-    // (with sweep blocks)
-    int best_mode = two_block_passes(c) ? 3 : 1;   // two passes run on the wave-per-block schedule only
+    // sweeps: one launch per wavefront (timed above), one workgroup per
+    // instance (a candidate only while wavefronts are narrow) or per sweep block
+    int best_mode = two_block_passes(c) ? 3 : 1;   // two passes run on the workgroup-per-block schedule only
     double best_sweep = best_t[3];
     for (int mode = 2; mode <= 3 && !rc && !two_block_passes(c); mode++) {
         if (mode == 2 && !((double)c->g.N / std::max(1, c->g.nlev) < 16384.0)) continue;

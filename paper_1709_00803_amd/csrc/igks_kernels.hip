@@ -20,6 +20,7 @@
 #include "igks_dev.h"
 
 #include <math.h>
+#include <type_traits>
 
 namespace igks {
 
@@ -499,7 +500,7 @@ __device__ __forceinline__ void msolve(double U, double V, double lam, double hl
 // LDS crossbar.  Both lanes of a pair are active together.
 __device__ __forceinline__ int pair_swap(int v)
 {
-    return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, false);
+    return __builtin_amdgcn_mov_dpp(v, 0xB1, 0xf, 0xf, true);
 }
 __device__ __forceinline__ double pair_other(double v)
 {
@@ -671,23 +672,42 @@ __device__ __forceinline__ void gks_finish(const GksEq &q, const double *acc, do
                q.T6 * f6[k];
 }
 
-// Euler flux Jacobian-vector product J(W, n) d (the linearised flux of the
-// implicit operator, Eq.18-20).  One reciprocal of rho: the sweeps run one
-// wavefront after another, and a divide is a long dependent sequence.
+// The term of one neighbour in the LU-SGS sweeps (Eq.18-20), split so that
+// everything that does not depend on the neighbour's increment can be formed
+// ahead of it: the Euler flux Jacobian J(W, n) in the products jac_apply
+// needs, half the face length, the dissipation and the SA off-diagonal
+// coefficient.  Which multiplies fuse with which adds is written out (no
+// contraction), so that the sweep schedules, which form the coefficients at
+// different places, give the same numbers.
 template <typename V>
-__device__ __forceinline__ void jac_vec(const V *W, V nx, V ny, const V *d, V *out)
+struct JacCoef {
+    V nx, ny, m1, m2, ir, u, v, q, ke, ep;   // normal, momentum, 1/rho, velocity, V.n, |V|^2/2, rho E + p
+};
+template <typename V>
+__device__ __forceinline__ JacCoef<V> jac_coef(const V *W, V nx, V ny)
 {
-    V r = W[0], ir = V(1) / r, U = W[1] * ir, Vv = W[2] * ir, E = W[3];
-    V ke = V(0.5) * (U * U + Vv * Vv);
-    V p = V(GAMMA - 1.0) * (E - r * ke);
-    V q = U * nx + Vv * ny;
-    V dmn = d[1] * nx + d[2] * ny;
-    V dq = (dmn - q * d[0]) * ir;
-    V dp = V(GAMMA - 1.0) * (d[3] - (U * d[1] + Vv * d[2]) + ke * d[0]);
+#pragma clang fp contract(off)
+    JacCoef<V> c;
+    const V r = W[0], E = W[3];
+    c.nx = nx; c.ny = ny; c.m1 = W[1]; c.m2 = W[2];
+    c.ir = V(1) / r;
+    c.u = W[1] * c.ir; c.v = W[2] * c.ir;
+    c.ke = V(0.5) * fma(c.u, c.u, c.v * c.v);
+    c.ep = fma(V(GAMMA - 1.0), fma(-r, c.ke, E), E);
+    c.q = fma(c.u, nx, c.v * ny);
+    return c;
+}
+template <typename V>
+__device__ __forceinline__ void jac_apply(const JacCoef<V> &c, const V *d, V *out)
+{
+#pragma clang fp contract(off)
+    const V dmn = fma(d[1], c.nx, d[2] * c.ny);
+    const V dq = fma(-c.q, d[0], dmn) * c.ir;
+    const V x = fma(c.ke, d[0], d[3] - fma(c.u, d[1], c.v * d[2])), dp = V(GAMMA - 1.0) * x;
     out[0] = dmn;
-    out[1] = d[1] * q + W[1] * dq + dp * nx;
-    out[2] = d[2] * q + W[2] * dq + dp * ny;
-    out[3] = (d[3] + dp) * q + (E + p) * dq;
+    out[1] = fma(dp, c.nx, fma(d[1], c.q, c.m1 * dq));
+    out[2] = fma(dp, c.ny, fma(d[2], c.q, c.m2 * dq));
+    out[3] = fma(c.ep, dq, fma(V(GAMMA - 1.0), x, d[3]) * c.q);
 }
 
 // ------------------------------------------------------------------ kernels
@@ -1358,7 +1378,7 @@ __device__ __forceinline__ V acc_add(V a, V b)
 template <int K>
 __device__ __forceinline__ int quad_get(int v)
 {
-    return __builtin_amdgcn_update_dpp(0, v, K * 0x55, 0xf, 0xf, false);
+    return __builtin_amdgcn_mov_dpp(v, K * 0x55, 0xf, 0xf, true);
 }
 template <int K>
 __device__ __forceinline__ float quad_get(float v)
@@ -1398,7 +1418,7 @@ constexpr double ROE_DELTA = 0.1;
 // inviscid part of the face's spectral radius; m0, m1, m3 the magnitudes of
 // the eigenvalues q - c, q, q + c
 struct RoeAvg {
-    double u, v, H, k, c, q, qt, smax, m0, m1, m3;
+    double u, v, H, k, c, q, qt, smax, m0, m1, m3, ic, g1c2;   // ic = 1/c, g1c2 = (gamma - 1)/c^2
 };
 
 __device__ __forceinline__ double kin_mag(double s, double rt2)
@@ -1419,6 +1439,8 @@ __device__ __forceinline__ RoeAvg roe_avg(const double *a, const double *b, doub
     R.H = (sa * (a[3] + pa) / ra + sb * (b[3] + pb) / rb) * iw;
     R.k = 0.5 * (R.u * R.u + R.v * R.v);
     R.c = sqrt(g1 * (R.H - R.k));
+    R.ic = 1.0 / R.c;
+    R.g1c2 = g1 * R.ic * R.ic;
     R.q = R.u * nx + R.v * ny;
     R.qt = -R.u * ny + R.v * nx;
     R.smax = fmax(fabs(ua * nx + va * ny) + sqrt(GAMMA * pa / ra), fabs(ub * nx + vb * ny) + sqrt(GAMMA * pb / rb));
@@ -1441,9 +1463,8 @@ __device__ __forceinline__ RoeAvg roe_avg(const double *a, const double *b, doub
 // eigenvalue magnitude, summed over the right eigenvectors
 __device__ __forceinline__ void roe_apply(const RoeAvg &R, double nx, double ny, const double *d, double *out)
 {
-    const double ic = 1.0 / R.c, g1c2 = (GAMMA - 1.0) * ic * ic;
-    const double dpc = g1c2 * (R.k * d[0] - R.u * d[1] - R.v * d[2] + d[3]);
-    const double dun = (-R.q * d[0] + nx * d[1] + ny * d[2]) * ic;
+    const double dpc = R.g1c2 * (R.k * d[0] - R.u * d[1] - R.v * d[2] + d[3]);
+    const double dun = (-R.q * d[0] + nx * d[1] + ny * d[2]) * R.ic;
     const double a0 = 0.5 * (dpc - dun) * R.m0;
     const double a3 = 0.5 * (dpc + dun) * R.m3;
     const double a1 = (d[0] - dpc) * R.m1;
@@ -1559,6 +1580,16 @@ __device__ __forceinline__ void dinv_apply(const Params<T> &P, int c, const T *x
     }
 }
 
+// Division by a cell's SA diagonal.  In FP64 by its reciprocal, which can be
+// formed before the numerator is known (the divide is a long dependent
+// sequence); in FP32 by the divide itself.
+template <typename T>
+struct SaDiag {
+    T v;
+    __device__ __forceinline__ explicit SaDiag(T d) : v(std::is_same_v<T, double> ? T(1) / d : d) {}
+    __device__ __forceinline__ T solve(T a) const { return std::is_same_v<T, double> ? a * v : a / v; }
+};
+
 // Forward-sweep increment dW*_j of a cell of the first wavefront: it has no
 // lower neighbours, so Eq.22 reduces to dW*_j = D_j^-1 M_j (the expressions
 // of sweep_cell with nothing subtracted, hence the same numbers).  Formed
@@ -1578,24 +1609,88 @@ __device__ __forceinline__ void first_front_incr(const Params<T> &P, const InstP
 #pragma unroll
         for (int k = 0; k < 4; k++) d[k] = T(P.M[k * N + j]) * iD;
     }
-    d[4] = ip.sa ? T(P.M[4 * N + j]) / (odt + T(P.sadiag[j])) : T(0);
+    d[4] = ip.sa ? SaDiag<T>(odt + T(P.sadiag[j])).solve(T(P.M[4 * N + j])) : T(0);
 }
 
-// Neighbour term of one cell-face entry in the LU-SGS sweeps (Eq.22 and
-// Eq.31-32): t[0..3] = (J(W_j, n) dW_j - lam dW_j) S / 2 with n pointing out
-// of the cell (the Roe operator: |A| + (lam - smax) I in place of lam,
-// except across sweep blocks, cross), t[4] = the SA off-diagonal coefficient
-// times dnu~_j, dW_j read from dsrc.  j < 0: the ghost cell, whose increment follows from the cell's
-// own dW* (Sec. 2.5).  Neighbours j < lev1 belong to the first wavefront,
-// whose forward increments are not stored (first_front_incr).
+// Coefficients of one cell-face entry's term in the sweeps; face: with the
+// Roe operator, whether the face keeps the scalar dissipation (one between
+// sweep blocks).
+template <typename T, bool ROE>
+struct TermCoef {
+    JacCoef<T> jac;
+    T h, lam, off;   // S/2, the dissipation lam (Roe: its viscous part lam - smax), the SA coefficient
+};
+template <typename T>
+struct TermCoef<T, true> {
+    JacCoef<T> jac;
+    T h, lam, off;
+    RoeAvg R;
+    double nx, ny;   // the Roe matrix acts in FP64
+    bool scalar;
+};
+template <typename T, bool ROE>
+__device__ __forceinline__ TermCoef<T, ROE> term_coef(const Params<T> &P, bool sa, const double *w, const double *wj,
+                                                      double nx, double ny, double S, double lam, double sak,
+                                                      bool cross)
+{
+    TermCoef<T, ROE> C;
+    const T wjt[4] = {T(wj[0]), T(wj[1]), T(wj[2]), T(wj[3])};
+    C.jac = jac_coef<T>(wjt, T(nx), T(ny));
+    C.h = T(0.5) * T(S);
+    C.lam = T(lam);
+    C.off = T(0);
+    if constexpr (ROE) {
+        C.scalar = cross;
+        C.nx = nx;
+        C.ny = ny;
+        if (!cross) {
+            C.R = roe_avg(w, wj, nx, ny, P.roe_kin);
+            C.lam = C.lam - T(C.R.smax);
+        }
+    }
+    if (sa) {
+#pragma clang fp contract(off)
+        const double qj = fma(wj[1], nx, wj[2] * ny) / wj[0];
+        C.off = T(fma(-0.5 * (qj - fabs(qj)), S, sak));
+    }
+    return C;
+}
+// t[0..3] = (J(W_j, n) dW_j - lam dW_j) S / 2 with n pointing out of the
+// cell (the Roe operator: |A| + (lam - smax) I in place of lam), t[4] = the
+// SA off-diagonal coefficient times dnu~_j (Eq.22, Eq.31-32).
+template <typename T, bool ROE>
+__device__ __forceinline__ void term_apply(const TermCoef<T, ROE> &C, const T *dj, T *t)
+{
+#pragma clang fp contract(off)
+    T jv[4];
+    jac_apply<T>(C.jac, dj, jv);
+    bool roe = false;
+    if constexpr (ROE) roe = !C.scalar;
+    if (roe) {
+        if constexpr (ROE) {
+            const double dd[4] = {double(dj[0]), double(dj[1]), double(dj[2]), double(dj[3])};
+            double ad[4];
+            roe_apply(C.R, C.nx, C.ny, dd, ad);
+#pragma unroll
+            for (int k = 0; k < 4; k++) t[k] = C.h * (fma(-C.lam, dj[k], jv[k]) - T(ad[k]));
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; k++) t[k] = C.h * fma(-C.lam, dj[k], jv[k]);
+    }
+    t[4] = C.off * dj[4];
+}
+
+// Neighbour term of one cell-face entry in the LU-SGS sweeps.  j < 0: the
+// ghost cell, whose increment follows from the cell's own dW* (Sec. 2.5).  Neighbours j < lev1 belong to the first
+// wavefront, whose forward increments are not stored (first_front_incr).
 template <typename T, bool ROE>
 __device__ __forceinline__ void sweep_term(const Params<T> &P, const InstParam &ip, const double *W,
                                            const double *w, int f, int e, int j, const T *dws, T cfl, int lev1,
-                                           T *t, const T *dsrc, bool cross = false)
+                                           T *t)
 {
     const int N = P.nc;
     double nx = P.enx[e], ny = P.eny[e];   // out of the cell
-    T S = T(P.es[e]), lam = T(P.flam[f]);
     double wj[5];
     T dj[5];
     if (j >= 0) {
@@ -1605,40 +1700,19 @@ __device__ __forceinline__ void sweep_term(const Params<T> &P, const InstParam &
             first_front_incr<T, ROE>(P, ip, j, cfl, dj);
         } else {
 #pragma unroll
-            for (int k = 0; k < 5; k++) dj[k] = dsrc[k * N + j];
+            for (int k = 0; k < 5; k++) dj[k] = P.dW[k * N + j];
         }
     } else {
         ghost(ip, P.fbc[f], w, nx, ny, wj);
         ghost_incr<T>(P.fbc[f], dws, T(nx), T(ny), T(wall_speed(ip, nx, ny)), dj);
     }
-    T wjt[4] = {T(wj[0]), T(wj[1]), T(wj[2]), T(wj[3])};
-    T jv[4];
-    jac_vec<T>(wjt, T(nx), T(ny), dj, jv);
-    T h = T(0.5) * S;
-    if (ROE && !cross) {
-        // (|A| + (lambda - smax) I) dW_j: the Roe matrix plus the viscous
-        // part of the spectral radius
-        const RoeAvg R = roe_avg(w, wj, nx, ny, P.roe_kin);
-        const double dd[4] = {double(dj[0]), double(dj[1]), double(dj[2]), double(dj[3])};
-        double ad[4];
-        roe_apply(R, nx, ny, dd, ad);
-        const T lv = lam - T(R.smax);
-#pragma unroll
-        for (int k = 0; k < 4; k++) t[k] = h * (jv[k] - lv * dj[k] - T(ad[k]));
-    } else {
-#pragma unroll
-        for (int k = 0; k < 4; k++) t[k] = h * (jv[k] - lam * dj[k]);
-    }
-    t[4] = T(0);
-    if (ip.sa) {
-        double qj = (wj[1] * nx + wj[2] * ny) / wj[0];
-        double off = -0.5 * (qj - fabs(qj)) * P.es[e] + P.fsak[f];
-        t[4] = T(off) * dj[4];
-    }
+    const TermCoef<T, ROE> C = term_coef<T, ROE>(P, ip.sa, w, wj, nx, ny, P.es[e], P.flam[f], ip.sa ? P.fsak[f] : 0.0,
+                                                 false);
+    term_apply<T, ROE>(C, dj, t);
 }
 
 // sweep modes
-enum { SW_FWD = 0, SW_BWD = 1, SW_TOP = 2, SW_BWD_ONLY = 3 };
+enum { SW_FWD = 0, SW_BWD = 1, SW_TOP = 2 };
 
 // W^{n+1} = W^n + dW (Eq.17) into the instance's other state buffer, nu~
 // clipped at 0; flags a non-physical result; returns the Eq.40 ratio
@@ -1704,108 +1778,15 @@ __global__ __launch_bounds__(256) void k_explicit(Params<T> P)
 // ghosts above them and their backward step needs nothing from other cells.
 // The backward step also applies W^{n+1} = W^n + dW (Eq.17) into the
 // instance's other state buffer (nu~ clipped at 0), flags a non-physical
-// result and returns the Eq.40 ratio; SW_BWD_ONLY leaves the update to
-// k_update.  inst = -1 for a frozen instance.
-template <typename T, int MODE, bool ONE, bool ROE>
-__device__ __forceinline__ double sweep_cell(const Params<T> &P, int c, int &inst)
-{
-    const int N = P.nc;
-    inst = live_inst<ONE>(P, P.cinst, c);
-    if (inst < 0) return 0.0;
-    const InstScalars &sc = P.is[inst];
-    const InstParam &ip = P.ip[inst];
-    const double *W = cur_state(P, inst);
-    const T cfl = T(sc.cfl);
-    double w[5];
-#pragma unroll
-    for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
-    const Entries E0 = entries(P, c);
-    const int ovf = next_block(P, E0);   // a polygon's overflow block, or -1
-    const T odt = T(P.lamc[c]) / cfl;   // Omega / dt_imp with dt_imp = CFL Omega / Lambda_c (Eq.24)
-    const T D = odt + T(P.lsum[c]);
-    T dws[5], acc[5], t[5];
-    if (MODE == SW_FWD || MODE == SW_TOP) {
-#pragma unroll
-        for (int k = 0; k < 5; k++) acc[k] = T(P.M[k * N + c]);
-        // lower neighbours of the cell's block; with two block passes, the
-        // second also takes every neighbour in another block, with the first
-        // pass's increment
-        auto lower = [&](const Entries &E, int b) {
-#pragma unroll
-            for (int k = 0; k < MAXV; k++) {
-                const int j = E.nbr[k], fl = E.flag[k];
-                if (!(fl & CF_VALID) || j < 0) continue;
-                const bool cross = (fl & CF_OTHER) && P.dWx;
-                if (!(fl & CF_LOWER) && !cross) continue;
-                sweep_term<T, ROE>(P, ip, W, w, E.face[k], MAXV * b + k, j, dws, cfl, 0, t, cross ? P.dWx : P.dW,
-                                   cross);
-#pragma unroll
-                for (int m = 0; m < 4; m++) acc[m] = acc_sub(acc[m], t[m]);
-                acc[4] = acc_add(acc[4], t[4]);
-            }
-        };
-        lower(E0, c);
-        if (ovf >= 0) lower(entries(P, ovf), ovf);
-        if (ROE) {
-            dinv_apply(P, c, acc, dws);
-        } else {
-            const T iD = T(1) / D;
-#pragma unroll
-            for (int k = 0; k < 4; k++) dws[k] = acc[k] * iD;
-        }
-        dws[4] = ip.sa ? acc[4] / (odt + T(P.sadiag[c])) : T(0);
-        if (MODE == SW_FWD) {
-#pragma unroll
-            for (int k = 0; k < 5; k++) P.dW[k * N + c] = dws[k];
-            return 0.0;
-        }
-    } else {
-#pragma unroll
-        for (int k = 0; k < 5; k++) dws[k] = P.dW[k * N + c];
-    }
-#pragma unroll
-    for (int k = 0; k < 5; k++) acc[k] = T(0);
-    auto upper = [&](const Entries &E, int b) {
-#pragma unroll
-        for (int k = 0; k < MAXV; k++) {
-            const int j = E.nbr[k], fl = E.flag[k];
-            if (!(fl & CF_VALID) || (j >= 0 && (fl & (CF_LOWER | CF_OTHER)))) continue;
-            sweep_term<T, ROE>(P, ip, W, w, E.face[k], MAXV * b + k, j, dws, cfl, 0, t, P.dW);
-#pragma unroll
-            for (int m = 0; m < 5; m++) acc[m] = acc_add(acc[m], t[m]);
-        }
-    };
-    upper(E0, c);
-    if (ovf >= 0) upper(entries(P, ovf), ovf);
-    T d[5];
-    if (ROE) {
-        T y[4];
-        dinv_apply(P, c, acc, y);
-#pragma unroll
-        for (int k = 0; k < 4; k++) d[k] = dws[k] - y[k];
-    } else {
-        const T iD = T(1) / D;
-#pragma unroll
-        for (int k = 0; k < 4; k++) d[k] = dws[k] - acc[k] * iD;
-    }
-    d[4] = ip.sa ? dws[4] + acc[4] / (odt + T(P.sadiag[c])) : T(0);
-#pragma unroll
-    for (int k = 0; k < 5; k++) P.dW[k * N + c] = d[k];
-    if (MODE == SW_BWD_ONLY) return 0.0;
-    double dd[5];
-#pragma unroll
-    for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
-    return apply_update(P, c, inst, w, dd);
-}
-
-// sweep_cell on a quad of lanes (q = 0..3, one cell per aligned quad): lane
+// result and returns the Eq.40 ratio.  inst = -1 for a frozen instance.
+//
+// A cell takes a quad of lanes (q = 0..3, one cell per aligned quad): lane
 // q takes entry q of each of the cell's entry blocks, so a cell's neighbour
 // terms are formed side by side instead of one after another, and the
-// terms are combined on every lane of the quad in entry order (quad_fold),
-// which gives the same numbers as sweep_cell.  Lane 0 stores and returns
-// the Eq.40 ratio; the other lanes return 0.  Cells below lev1 (the first
-// wavefront) have no stored forward increment: their own and their
-// neighbours' are formed by first_front_incr.
+// terms are combined on every lane of the quad in entry order (quad_fold).
+// Lane 0 stores and returns the Eq.40 ratio; the other lanes return 0.
+// Cells below lev1 (the first wavefront) have no stored forward increment:
+// their own and their neighbours' are formed by first_front_incr.
 template <typename T, int MODE, bool ONE, bool ROE>
 __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, int lev1, int &inst)
 {
@@ -1828,15 +1809,11 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
     if (MODE == SW_FWD || MODE == SW_TOP) {
 #pragma unroll
         for (int k = 0; k < 5; k++) acc[k] = T(P.M[k * N + c]);
-        // lower neighbours of the cell's block; with two block passes, the
-        // second also takes every neighbour in another block, with the first
-        // pass's increment
         auto lower = [&](int f, int e, int j, int fl) {
 #pragma unroll
             for (int m = 0; m < 5; m++) t[m] = T(0);
-            const bool cross = (fl & CF_OTHER) && P.dWx;
-            if ((fl & CF_VALID) && j >= 0 && ((fl & CF_LOWER) || cross))
-                sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, cross ? 0 : lev1, t, cross ? P.dWx : P.dW, cross);
+            if ((fl & CF_VALID) && j >= 0 && (fl & CF_LOWER))
+                sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, lev1, t);
 #pragma unroll
             for (int m = 0; m < 4; m++) acc[m] = quad_fold<true>(acc[m], t[m]);
             acc[4] = quad_fold<false>(acc[4], t[4]);
@@ -1851,7 +1828,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
             for (int k = 0; k < 4; k++) dws[k] = acc[k] * iD;
         }
-        dws[4] = ip.sa ? acc[4] / (odt + T(P.sadiag[c])) : T(0);
+        dws[4] = ip.sa ? SaDiag<T>(odt + T(P.sadiag[c])).solve(acc[4]) : T(0);
         if (MODE == SW_FWD) {
             if (q == 0) {
 #pragma unroll
@@ -1871,7 +1848,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
         for (int m = 0; m < 5; m++) t[m] = T(0);
         if ((fl & CF_VALID) && !(j >= 0 && (fl & (CF_LOWER | CF_OTHER))))
-            sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, lev1, t, P.dW);
+            sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, lev1, t);
 #pragma unroll
         for (int m = 0; m < 5; m++) acc[m] = quad_fold<false>(acc[m], t[m]);
     };
@@ -1890,10 +1867,9 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
         for (int k = 0; k < 4; k++) d[k] = dws[k] - acc[k] * iD;
     }
-    d[4] = ip.sa ? dws[4] + acc[4] / (odt + T(P.sadiag[c])) : T(0);
+    d[4] = ip.sa ? acc_add(dws[4], SaDiag<T>(odt + T(P.sadiag[c])).solve(acc[4])) : T(0);
 #pragma unroll
     for (int k = 0; k < 5; k++) P.dW[k * N + c] = d[k];
-    if (MODE == SW_BWD_ONLY) return 0.0;
     double dd[5];
 #pragma unroll
     for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
@@ -1953,53 +1929,404 @@ __global__ __launch_bounds__(256) void k_sweep(Params<T> P, int c0, int c1, int 
     if (MODE != SW_FWD) slot_update<false>(P.slot, SL_E40, inst, e);
 }
 
-// The whole sweep in one workgroup: wavefront after wavefront, separated by
-// workgroup barriers (all waves of a workgroup share one CU and its L1, so
-// the barrier orders the dW writes of one wavefront before the reads of the
-// next).  Used when wavefronts are many and narrow: the time per wavefront
-// is latency, so the backward sweep leaves the update (Eq.17, Eq.40) to one
-// parallel pass afterwards (k_update) instead of adding its loads and stores
-// to every step.
-// ONE (a context of one instance) makes the instance index a constant, so
-// its scalars come through scalar loads instead of a dependent vector load
-// chain on every wavefront.
-template <typename T, bool FWD, bool ONE, bool ROE>
-__global__ __launch_bounds__(512) void k_sweep_wg(Params<T> P, const int *lev_off, int nlev)
+// The whole sweep of one group of cells (a sweep block, or an instance that
+// has none) by one workgroup, its wavefronts one after another.  Used when
+// wavefronts are many and narrow.  Groups do not couple in the sweeps, so no
+// workgroup waits for another.
+//
+// A wavefront is cut into chunks of 16 cells, four lanes per cell (lane q
+// has entry q, as in sweep_quad), and the chunks are dealt to the workgroup's
+// waves in turn.  The time per wavefront is a chain of latencies, so all that
+// does not need the other cells' increments is taken out of it: while
+// earlier chunks run on the other waves, a wave loads what its next chunk
+// needs (the entries one turn earlier still) and forms the terms'
+// coefficients.  The increments themselves pass through LDS, a ring of slots
+// in sweep order (cslot); the chunk is run once the chunks of all earlier
+// wavefronts are counted complete, and adds itself to the count.  What is
+// left in the chain is one LDS read, the product with the increments, the
+// sum over the quad and one LDS write.
+//
+// No wave waits without end: a wave takes its chunks in order, and a chunk
+// waits only for earlier chunks of the same workgroup, whose waves are all
+// resident, so the first unfinished chunk can always run; the poll is
+// bounded all the same, and a wave that ran out of polls marks the
+// instance's update as bad.
+//
+// Measured (forward + backward sweep with its update, us), against a wave per
+// block that loaded everything in its turn: 64x32 plate in blocks of 128,
+// 92 -> 38; turbulent plate (100 wavefronts a block) 388 -> 103; 41k aerofoil
+// in blocks of 256, FP32, 119 -> 47; 250k aerofoil, two passes, 745 -> 254;
+// against one workgroup with a barrier after each wavefront: the polygon
+// cavity in its own order (385 wavefronts) 1940 -> 495.  About 0.37 us a
+// forward wavefront of one chunk, of which the chain's instructions (95
+// FP64 and lane moves at 4 or more cycles) are half and its two LDS trips
+// most of the rest.
+//
+// The terms and their order are those of sweep_quad, so the iterates are
+// bitwise those of the launch-per-wavefront schedule.  The backward sweep
+// leaves the update (Eq.17, Eq.40) to one parallel pass afterwards (k_update).
+constexpr unsigned SPIN_LIMIT = 1u << 22;
+
+// A chunk's cells [x, y) and the chunks that must be complete before it in
+// the forward (z) and the backward sweep (w); y <= x past the group's end.
+// Through a vector load: scalar loads share their counter with the LDS
+// accesses of the chain.  (Here and below nothing is loaded under a branch:
+// a lane without a cell or an entry loads from a place that exists, since the
+// wait for a load would move to where the branches meet again.)
+template <bool FWD>
+__device__ __forceinline__ int4 chunk_place(const int4 *chunk, int i, int n)
 {
-    for (int i = 0; i < nlev; i++) {
-        int l = FWD ? i : nlev - 1 - i;
-        int c0 = lev_off[l], c1 = lev_off[l + 1];
-        for (int c = c0 + (int)threadIdx.x; c < c1; c += (int)blockDim.x) {
-            int inst;
-            (void)sweep_cell<T, FWD ? SW_FWD : SW_BWD_ONLY, ONE, ROE>(P, c, inst);
+    int k = min(i, n - 1);
+    if (!FWD) k = n - 1 - k;
+    asm volatile("" : "+v"(k));
+    int4 m = chunk[k];
+    if (i >= n) m.y = -1;
+    return m;
+}
+// a lane's cell and entry
+struct ChunkIdx {
+    int need, c, e, f, j, fl;
+    bool act;   // the lane has a cell
+};
+enum { SRC_NONE = 0, SRC_NEAR = 1, SRC_CROSS = 2, SRC_GHOST = 3 };
+// what a lane loads for its entry and its cell
+template <typename T, bool FWD, bool TWO, bool ROE>
+struct ChunkRaw {
+    using Rhs = std::conditional_t<FWD, double, T>;   // M, or the forward sweep's increment
+    int src, bc, slot_c, slot_j, ovf;   // src: SRC_*
+    double w[5], nx, ny, S, lam, sak, lamc, lsum, sadiag;
+    Rhs rhs[5];
+    T dx[TWO ? 5 : 1];        // a first block pass's increment of the neighbour
+    double wc[ROE ? 5 : 1];   // Roe operator: the cell's own state,
+    T di[ROE ? 4 : 1];        // row q of its inverted diagonal block
+};
+
+template <typename T, bool FWD>
+__device__ __forceinline__ ChunkIdx chunk_entries(const Params<T> &P, const int4 &m, int q, int cell)
+{
+    ChunkIdx I;
+    I.act = m.x + cell < m.y;
+    I.need = FWD ? m.z : m.w;
+    I.c = min(m.x + cell, P.nc - 1);
+    I.e = MAXV * I.c + q;
+    I.f = P.cf_face[I.e];
+    I.j = P.cf_nbr[I.e];
+    I.fl = P.cf_flag[I.e];
+    return I;
+}
+// which term an entry has in this sweep
+template <bool FWD, bool TWO>
+__device__ __forceinline__ int entry_source(int j, int fl)
+{
+    if (!(fl & CF_VALID)) return SRC_NONE;
+    if (FWD) {
+        if (j < 0) return SRC_NONE;
+        if (fl & CF_LOWER) return SRC_NEAR;
+        return ((fl & CF_OTHER) && TWO) ? SRC_CROSS : SRC_NONE;
+    }
+    if (j < 0) return SRC_GHOST;
+    return (fl & (CF_LOWER | CF_OTHER)) ? SRC_NONE : SRC_NEAR;
+}
+// the loads of one entry's term (a ghost's state follows from the cell's)
+template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
+__device__ __forceinline__ void entry_gather(const Params<T> &P, const double *W, const int *cslot, int c, int e,
+                                             int f, int j, int fl, ChunkRaw<T, FWD, TWO, ROE> &R)
+{
+    const int N = P.nc, jw = j >= 0 ? j : c;
+    R.src = entry_source<FWD, TWO>(j, fl);
+#pragma unroll
+    for (int k = 0; k < 5; k++) R.w[k] = W[k * N + jw];
+    R.nx = P.enx[e]; R.ny = P.eny[e]; R.S = P.es[e];
+    R.lam = P.flam[f];
+    R.sak = P.fsak[f];
+    R.bc = P.fbc[f];
+    R.slot_j = RING ? cslot[jw] : jw;
+    if constexpr (TWO) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) R.dx[k] = P.dWx[k * N + jw];
+    }
+}
+template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
+__device__ __forceinline__ void chunk_gather(const Params<T> &P, const double *W, const int *cslot, int q,
+                                             const ChunkIdx &I, ChunkRaw<T, FWD, TWO, ROE> &R)
+{
+    const int N = P.nc, c = I.c;
+    entry_gather<T, FWD, TWO, RING, ROE>(P, W, cslot, c, I.e, I.f, I.j, I.fl, R);
+    if (!I.act) R.src = SRC_NONE;
+    const int nxt = quad_get<3>(I.fl) >> CF_NEXT_SHIFT;
+    R.ovf = I.act && nxt ? N + nxt - 1 : -1;   // a polygon's overflow block, or -1
+    R.slot_c = cslot[c];
+    R.lamc = P.lamc[c]; R.lsum = P.lsum[c]; R.sadiag = P.sadiag[c];
+#pragma unroll
+    for (int k = 0; k < 5; k++) {
+        if constexpr (FWD) R.rhs[k] = P.M[k * N + c];
+        else R.rhs[k] = P.dW[k * N + c];
+    }
+    if constexpr (ROE) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) R.wc[k] = W[k * N + c];
+#pragma unroll
+        for (int k = 0; k < 4; k++) R.di[k] = P.dinv[(4 * q + k) * N + c];
+    }
+}
+template <typename T, bool FWD, bool TWO, bool ROE>
+__device__ __forceinline__ TermCoef<T, ROE> entry_coef(const Params<T> &P, const InstParam &ip,
+                                                       const ChunkRaw<T, FWD, TWO, ROE> &R)
+{
+    double g[5] = {R.w[0], R.w[1], R.w[2], R.w[3], R.w[4]};
+    if (!FWD && R.src == SRC_GHOST) ghost(ip, R.bc, R.w, R.nx, R.ny, g);
+    const double *wc = R.w;
+    if constexpr (ROE) wc = R.wc;
+    return term_coef<T, ROE>(P, ip.sa, wc, g, R.nx, R.ny, R.S, R.lam, R.sak, R.src == SRC_CROSS);
+}
+// x is computed here: the compiler would move what only the chunk's turn uses
+// into it
+template <typename V>
+__device__ __forceinline__ void pin(V &x)
+{
+    asm volatile("" : "+v"(x));
+}
+template <typename T, bool ROE>
+__device__ __forceinline__ void pin_coef(TermCoef<T, ROE> &C)
+{
+    pin(C.jac.nx); pin(C.jac.ny); pin(C.jac.m1); pin(C.jac.m2); pin(C.jac.ir);
+    pin(C.jac.u); pin(C.jac.v); pin(C.jac.q); pin(C.jac.ke); pin(C.jac.ep);
+    pin(C.h); pin(C.lam); pin(C.off);
+    if constexpr (ROE) {
+        pin(C.R.u); pin(C.R.v); pin(C.R.H); pin(C.R.k); pin(C.R.c); pin(C.R.q); pin(C.R.qt);
+        pin(C.R.m0); pin(C.R.m1); pin(C.R.m3); pin(C.R.ic); pin(C.R.g1c2);
+    }
+}
+// An entry that has no term here gets the coefficients 0: its slot holds a
+// finite increment (the ring starts at 0), or a non-finite one of an update
+// that is going to be rejected.
+template <typename T, bool ROE>
+__device__ __forceinline__ void no_term(TermCoef<T, ROE> &C, bool none)
+{
+    C.h = none ? T(0) : C.h;
+    C.off = none ? T(0) : C.off;
+}
+// the neighbour's increment: from LDS, or without the ring from global memory
+template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
+__device__ __forceinline__ void entry_incr(const Params<T> &P, const ChunkRaw<T, FWD, TWO, ROE> &R, const T *dw, T *d)
+{
+    const int N = P.nc;
+    if constexpr (RING) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) d[k] = dw[5 * R.slot_j + k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 5; k++) d[k] = T(0);
+        if (R.src == SRC_NEAR) {
+#pragma unroll
+            for (int k = 0; k < 5; k++) d[k] = P.dW[k * N + R.slot_j];
         }
-        __syncthreads();
+    }
+}
+// the term: with that increment, that of the first block pass, or the ghost's
+// from the cell's own
+template <typename T, bool FWD, bool TWO, bool ROE>
+__device__ __forceinline__ void entry_term(const InstParam &ip, const ChunkRaw<T, FWD, TWO, ROE> &R,
+                                           const TermCoef<T, ROE> &C, const T *dws, T *d, T *t)
+{
+    if constexpr (TWO) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) d[k] = R.src == SRC_CROSS ? R.dx[k] : d[k];
+    }
+    if (!FWD && R.src == SRC_GHOST)
+        ghost_incr<T>(R.bc, dws, T(R.nx), T(R.ny), T(wall_speed(ip, R.nx, R.ny)), d);
+    term_apply<T, ROE>(C, d, t);
+}
+
+// what the chunks of a group share
+template <typename T>
+struct GroupRun {
+    const double *W;
+    const int *cslot;
+    const int4 *chunk;
+    T *dw;             // the ring
+    unsigned *done;    // finished chunks
+    T cfl;
+    int n, q, cell, nw, inst;
+};
+// Chunk i of the wave (loaded: A): the next chunk's loads into Rn (entries
+// In), the entries of the one after it into I, its place in `place`; this
+// chunk's coefficients; then the chunk itself.
+template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
+__device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam &ip, const GroupRun<T> &G, int i,
+                                            const ChunkRaw<T, FWD, TWO, ROE> &A, ChunkIdx &I,
+                                            ChunkRaw<T, FWD, TWO, ROE> &Rn, const ChunkIdx &In, int4 &place)
+{
+    const int N = P.nc, q = G.q;
+    const bool sa = ip.sa;
+    const int c = I.c, need = __builtin_amdgcn_readfirstlane(I.need);
+    const bool store = q == 0 && I.act;
+    chunk_gather<T, FWD, TWO, RING, ROE>(P, G.W, G.cslot, q, In, Rn);
+    I = chunk_entries<T, FWD>(P, place, q, G.cell);
+    place = chunk_place<FWD>(G.chunk, i + 3 * G.nw, G.n);
+    TermCoef<T, ROE> C = entry_coef<T, FWD, TWO, ROE>(P, ip, A);
+    no_term(C, A.src == SRC_NONE);
+    pin_coef(C);
+    T rhs[5];
+#pragma unroll
+    for (int k = 0; k < 5; k++) {
+        rhs[k] = T(A.rhs[k]);
+        pin(rhs[k]);
+    }
+    const T odt = T(A.lamc) / G.cfl;
+    T iD = T(1) / (odt + T(A.lsum));
+    SaDiag<T> Ds(sa ? odt + T(A.sadiag) : T(1));
+    pin(iD);
+    pin(Ds.v);
+    // the entries of polygons beyond the fourth, formed ahead too unless the
+    // Roe matrices take the registers
+    ChunkRaw<T, FWD, TWO, ROE> B;
+    TermCoef<T, ROE> CB;
+    const bool poly = __any(A.ovf >= 0);
+    auto overflow = [&]() {
+        const int b = A.ovf >= 0 ? A.ovf : c, e = MAXV * b + q;
+        if constexpr (ROE) {
+#pragma unroll
+            for (int k = 0; k < 5; k++) B.wc[k] = A.wc[k];
+        }
+        entry_gather<T, FWD, TWO, RING, ROE>(P, G.W, G.cslot, c, e, P.cf_face[e], P.cf_nbr[e], P.cf_flag[e], B);
+        if (A.ovf < 0) B.src = SRC_NONE;
+        CB = entry_coef<T, FWD, TWO, ROE>(P, ip, B);
+        no_term(CB, B.src == SRC_NONE);
+        pin_coef(CB);
+    };
+    if (!ROE && poly) overflow();
+    // its turn: every chunk of the earlier wavefronts is complete.  The LDS
+    // executes a wave's operations in order, so the increments read after
+    // the count are at least as new as it, and the count is raised after the
+    // increments are written (without the ring they pass through global
+    // memory and the fences wait for it).
+    // Until one chunk is missing only the count is read: the polls of the
+    // waiting waves would fill the LDS.
+    T t[5], acc[5], d[5];
+    unsigned spin = 0, done;
+    __builtin_amdgcn_s_setprio(0);
+#pragma unroll 1
+    do {
+        done = __hip_atomic_load(G.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } while (done + 1 < (unsigned)need && ++spin < SPIN_LIMIT);
+#pragma unroll 1
+    do {
+        done = __hip_atomic_load(G.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (RING) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            entry_incr<T, FWD, TWO, RING, ROE>(P, A, G.dw, d);
+#pragma unroll
+            for (int k = 0; k < 5; k++) pin(d[k]);
+        }
+    } while (done < (unsigned)need && ++spin < SPIN_LIMIT);
+    __builtin_amdgcn_s_setprio(3);   // the others wait for this wave
+    if constexpr (!RING) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        entry_incr<T, FWD, TWO, RING, ROE>(P, A, G.dw, d);
+    }
+    entry_term<T, FWD, TWO, ROE>(ip, A, C, rhs, d, t);
+    if (FWD) {
+        // M less the lower neighbours' terms
+#pragma unroll
+        for (int m = 0; m < 4; m++) acc[m] = quad_fold<true>(rhs[m], t[m]);
+        acc[4] = quad_fold<false>(rhs[4], t[4]);
+    } else {
+#pragma unroll
+        for (int m = 0; m < 5; m++) acc[m] = quad_fold<false>(T(0), t[m]);
+    }
+    if (poly) {
+        if (ROE) overflow();
+        entry_incr<T, FWD, TWO, RING, ROE>(P, B, G.dw, d);
+        entry_term<T, FWD, TWO, ROE>(ip, B, CB, rhs, d, t);
+#pragma unroll
+        for (int m = 0; m < 4; m++) acc[m] = quad_fold<FWD>(acc[m], t[m]);
+        acc[4] = quad_fold<false>(acc[4], t[4]);
+    }
+    if constexpr (ROE) {
+        // row q of D^-1 acc on lane q (the order of dinv_apply)
+        T y = A.di[0] * acc[0];
+#pragma unroll
+        for (int k = 1; k < 4; k++) y = fma(A.di[k], acc[k], y);
+        d[0] = quad_get<0>(y); d[1] = quad_get<1>(y); d[2] = quad_get<2>(y); d[3] = quad_get<3>(y);
+#pragma unroll
+        for (int k = 0; k < 4; k++) d[k] = FWD ? d[k] : rhs[k] - d[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; k++) d[k] = FWD ? acc[k] * iD : rhs[k] - acc[k] * iD;
+    }
+    if (FWD) d[4] = sa ? Ds.solve(acc[4]) : T(0);
+    else d[4] = sa ? acc_add(rhs[4], Ds.solve(acc[4])) : T(0);
+    if (store) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) {
+            if (RING) G.dw[5 * A.slot_c + k] = d[k];
+            else P.dW[k * N + c] = d[k];
+        }
+    }
+    if (RING) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (((int)threadIdx.x & 63) == 0) {
+        __hip_atomic_fetch_add(G.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (spin >= SPIN_LIMIT) atomicOr(&P.is[G.inst].bad, 1);
+    }
+    __builtin_amdgcn_s_setprio(1);
+    if (RING && store) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) P.dW[k * N + c] = d[k];
+    }
+}
+// The wave's chunks, two sets of registers in turn.
+template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
+__device__ __forceinline__ void group_sweep(const Params<T> &P, const InstParam &ip, const GroupRun<T> &G, int wave)
+{
+    ChunkIdx I0 = chunk_entries<T, FWD>(P, chunk_place<FWD>(G.chunk, wave, G.n), G.q, G.cell);
+    ChunkIdx I1 = chunk_entries<T, FWD>(P, chunk_place<FWD>(G.chunk, wave + G.nw, G.n), G.q, G.cell);
+    int4 place = chunk_place<FWD>(G.chunk, wave + 2 * G.nw, G.n);
+    ChunkRaw<T, FWD, TWO, ROE> R0, R1;
+    chunk_gather<T, FWD, TWO, RING, ROE>(P, G.W, G.cslot, G.q, I0, R0);
+    for (int i = wave; i < G.n; i += 2 * G.nw) {
+        group_chunk<T, FWD, TWO, RING, ROE>(P, ip, G, i, R0, I0, R1, I1, place);
+        if (i + G.nw >= G.n) break;
+        group_chunk<T, FWD, TWO, RING, ROE>(P, ip, G, i + G.nw, R1, I1, R0, I0, place);
     }
 }
 
-// The whole sweep of one sweep block per wave: the block's wavefronts one
-// after another, each cell of a wavefront on a quad of lanes (lane q forms
-// the term of entry q, sweep_quad; 16 cells per step, and a block's
-// wavefront holds a few cells).  Blocks do not couple in the sweeps, so no
-// wave waits for another; inside the one-wave workgroup the barrier after
-// each wavefront orders its dW writes before the next wavefront's reads.
-// As in the one-workgroup sweep, the backward pass leaves the update to
-// k_update.
-template <typename T, bool FWD, bool ONE, bool ROE>
-__global__ __launch_bounds__(64) void k_sweep_blk(Params<T> P, const int *bl_off, const int *bl_lo, const int *bl_hi)
+// cslot: LDS slot of each cell, negative in a group whose couplings span more
+// cells than the ring holds: its increments pass through global memory
+// instead.  chunk[ch_off[g] .. ch_off[g + 1]): the group's chunks in forward
+// order.  Dynamic LDS: the ring of `slots` increments, then the count of
+// finished chunks.  TWO: the forward sweep of a second block pass.
+template <typename T, bool FWD, bool TWO, bool ONE, bool ROE>
+__global__ __launch_bounds__(512) void k_sweep_grp(Params<T> P, const int *cslot, const int *ch_off,
+                                                   const int4 *chunk, int slots)
 {
-    const int gb = blockIdx.x;
-    const int k0 = bl_off[gb], k1 = bl_off[gb + 1];
-    const int q = (int)threadIdx.x & 3, cell = (int)threadIdx.x >> 2;
-    for (int i = 0; i < k1 - k0; i++) {
-        const int k = FWD ? k0 + i : k1 - 1 - i;
-        const int c0 = bl_lo[k], c1 = bl_hi[k];
-        for (int c = c0 + cell; c < c1; c += 16) {   // the four lanes of a quad take the same cell
-            int inst;
-            (void)sweep_quad<T, FWD ? SW_FWD : SW_BWD_ONLY, ONE, ROE>(P, c, q, 0, inst);
-        }
-        __syncthreads();
-    }
+    extern __shared__ __align__(16) unsigned char smem[];
+    GroupRun<T> G;
+    G.dw = reinterpret_cast<T *>(smem);
+    G.done = reinterpret_cast<unsigned *>(smem + sizeof(T) * 5 * (size_t)slots);
+    const int k0 = ch_off[blockIdx.x];
+    G.n = ch_off[blockIdx.x + 1] - k0;
+    if (G.n <= 0) return;
+    G.chunk = chunk + k0;
+    G.cslot = cslot;
+    const int c0 = G.chunk[0].x;
+    // a group's cells belong to one instance
+    G.inst = ONE ? 0 : __builtin_amdgcn_readfirstlane(cell_inst(P, c0));
+    if (!ONE && P.is[G.inst].halt) return;   // the whole workgroup
+    const InstParam ip = P.ip[G.inst];
+    G.W = cur_state(P, G.inst);
+    G.cfl = T(P.is[G.inst].cfl);
+    const int lane = (int)threadIdx.x & 63;
+    G.q = lane & 3;
+    G.cell = lane >> 2;
+    G.nw = (int)blockDim.x >> 6;
+    for (int k = threadIdx.x; k < 5 * slots; k += blockDim.x) G.dw[k] = T(0);
+    if (threadIdx.x == 0) *G.done = 0u;
+    __syncthreads();
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (__builtin_amdgcn_readfirstlane(cslot[c0]) >= 0) group_sweep<T, FWD, TWO, true, ROE>(P, ip, G, wave);
+    else group_sweep<T, FWD, TWO, false, ROE>(P, ip, G, wave);
 }
 
 // W^{n+1} = W^n + dW for every cell from the finished backward sweep (the
@@ -2133,6 +2460,16 @@ template <typename T> void launch_reduce(const Launch &L, const Params<T> &P, in
         else hipLaunchKernelGGL((K<T, X, false, true>), grid, block, 0, L.s, __VA_ARGS__);               \
     } while (0)
 
+template <typename T, bool FWD, bool TWO>
+static void launch_grp(const Launch &L, const Params<T> &P, const SweepGroups &G)
+{
+    const bool one = P.ninst == 1, roe = P.dinv != nullptr;
+    auto *k = one ? (roe ? k_sweep_grp<T, FWD, TWO, true, true> : k_sweep_grp<T, FWD, TWO, true, false>)
+                  : (roe ? k_sweep_grp<T, FWD, TWO, false, true> : k_sweep_grp<T, FWD, TWO, false, false>);
+    hipLaunchKernelGGL(k, dim3(G.n), dim3(64 * G.waves), grp_lds(G.slots, sizeof(T)), L.s, P, G.cslot, G.ch_off,
+                       G.chunk, G.slots);
+}
+
 template <typename T> void launch_sweep(const Launch &L, const Params<T> &P, int c0, int c1, int mode, int lev1)
 {
     if (c1 <= c0) return;
@@ -2141,26 +2478,14 @@ template <typename T> void launch_sweep(const Launch &L, const Params<T> &P, int
     else if (mode == SW_BWD) LAUNCH_SWEEP(k_sweep, SW_BWD, g, b, P, c0, c1, lev1);
     else LAUNCH_SWEEP(k_sweep, SW_TOP, g, b, P, c0, c1, lev1);
 }
-template <typename T> void launch_sweep_wg(const Launch &L, const Params<T> &P, const int *lev_off, int nlev, bool fwd)
-{
-    if (fwd) {
-        LAUNCH_SWEEP(k_sweep_wg, true, dim3(1), dim3(512), P, lev_off, nlev);
-    } else {
-        LAUNCH_SWEEP(k_sweep_wg, false, dim3(1), dim3(512), P, lev_off, nlev);
-        LAUNCH_ONE(k_update, T, dim3(nblk(P.nc, L.block[3])), dim3(L.block[3]), P);
-    }
-}
 template <typename T>
-void launch_sweep_blk(const Launch &L, const Params<T> &P, const int *bl_off, const int *bl_lo, const int *bl_hi,
-                      int ngb, bool fwd, bool update)
+void launch_sweep_grp(const Launch &L, const Params<T> &P, const SweepGroups &G, bool fwd, bool update)
 {
-    if (ngb <= 0) return;
-    if (fwd) {
-        LAUNCH_SWEEP(k_sweep_blk, true, dim3(ngb), dim3(64), P, bl_off, bl_lo, bl_hi);
-    } else {
-        LAUNCH_SWEEP(k_sweep_blk, false, dim3(ngb), dim3(64), P, bl_off, bl_lo, bl_hi);
-        if (update) LAUNCH_ONE(k_update, T, dim3(nblk(P.nc, L.block[3])), dim3(L.block[3]), P);
-    }
+    if (G.n <= 0) return;
+    if (!fwd) launch_grp<T, false, false>(L, P, G);
+    else if (P.dWx) launch_grp<T, true, true>(L, P, G);
+    else launch_grp<T, true, false>(L, P, G);
+    if (update) LAUNCH_ONE(k_update, T, dim3(nblk(P.nc, L.block[3])), dim3(L.block[3]), P);
 }
 template <typename T> void launch_roe_diag(const Launch &L, const Params<T> &P)
 {
@@ -2200,9 +2525,7 @@ void launch_copy_instance(const Launch &L, int n, const int *cells, int nc, cons
     template void launch_sweep<T>(const Launch &, const Params<T> &, int, int, int, int);          \
     template void launch_commit<T>(const Launch &, const Params<T> &, int);                        \
     template void launch_explicit<T>(const Launch &, const Params<T> &);                           \
-    template void launch_sweep_wg<T>(const Launch &, const Params<T> &, const int *, int, bool);                 \
-    template void launch_sweep_blk<T>(const Launch &, const Params<T> &, const int *, const int *, const int *,  \
-                                      int, bool, bool);
+    template void launch_sweep_grp<T>(const Launch &, const Params<T> &, const SweepGroups &, bool, bool);
 INST(double)
 INST(float)
 

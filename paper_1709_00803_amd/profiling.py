@@ -22,6 +22,8 @@ def kernel_class(name: str):
     """Kernel class of a (demangled) kernel name, as bench.py reports them."""
     table = [("k_prep", "prep"), ("k_flux2", "flux2"), ("k_flux", "flux"), ("k_gather", "gather"),
              ("k_reduce", "reduce"), ("k_commit", "commit"),
+             ("k_sweep_grp<double, true", "sweep_fwd"), ("k_sweep_grp<double, false", "sweep_bwd"),
+             ("k_sweep_grp<float, true", "sweep_fwd"), ("k_sweep_grp<float, false", "sweep_bwd"),
              ("k_sweep_wg<double, true", "sweep_fwd"), ("k_sweep_wg<double, false", "sweep_bwd"),
              ("k_sweep_wg<float, true", "sweep_fwd"), ("k_sweep_wg<float, false", "sweep_bwd"),
              ("k_sweep<double, 0,", "sweep_fwd"), ("k_sweep<double, 2,", "sweep_top"),
