@@ -338,6 +338,16 @@ __device__ __forceinline__ Entries entries(const Params<T> &P, int b)
     const int4 g = reinterpret_cast<const int4 *>(P.cf_flag)[b];
     return Entries{{f.x, f.y, f.z, f.w}, {n.x, n.y, n.z, n.w}, {g.x, g.y, g.z, g.w}};
 }
+// the four values of block b of an entry array, two 16-byte loads
+struct Quad {
+    double v[MAXV];
+};
+__device__ __forceinline__ Quad quad4(const double *a, int b)
+{
+    const double2 *p = reinterpret_cast<const double2 *>(a) + 2 * (size_t)b;
+    const double2 x = p[0], y = p[1];
+    return Quad{{x.x, x.y, y.x, y.y}};
+}
 // the block after E, or -1 (triangles and quadrilaterals have one block)
 template <typename T>
 __device__ __forceinline__ int next_block(const Params<T> &P, const Entries &E)
@@ -754,30 +764,34 @@ __device__ __forceinline__ double prep_cell(const Params<T> &P, int c, int inst)
     double lc = 0.0, b1[4] = {0, 0, 0, 0}, b2[4] = {0, 0, 0, 0}, wmax[4], wmin[4];
 #pragma unroll
     for (int k = 0; k < 4; k++) wmax[k] = wmin[k] = w[k];
-    // the cell's block, then a polygon's overflow block (a rarely taken branch,
-    // so triangles and quadrilaterals run straight-line code)
+    // The cell's block, then a polygon's overflow block (a rarely taken branch,
+    // so triangles and quadrilaterals run straight-line code).  All loads of a
+    // block are issued before any is used, under no branch (a branch's loads
+    // are waited for where it ends, one entry after another): an entry that
+    // does not exist has length and offsets 0 and, like a ghost, the cell's own
+    // state in place of a neighbour's.
     auto block = [&](const Entries &E, int b) {
+        const Quad nx = quad4(P.enx, b), ny = quad4(P.eny, b), S = quad4(P.es, b);
+        const Quad dx = quad4(P.cf_dx, b), dy = quad4(P.cf_dy, b);
+        double wj[MAXV][5];
 #pragma unroll
         for (int k = 0; k < MAXV; k++) {
-            if (!(E.flag[k] & CF_VALID)) continue;
-            const int e = MAXV * b + k, f = E.face[k], j = E.nbr[k];
-            double nx = P.enx[e], ny = P.eny[e], S = P.es[e];   // the outward normal of a boundary face
-            lc += (fabs(U * nx + V * ny) + cs) * S;
-            double wj[5];
-            if (j >= 0) {
+            const int j = E.nbr[k] >= 0 ? E.nbr[k] : c;
 #pragma unroll
-                for (int k = 0; k < 4; k++) wj[k] = W[k * N + j];
-            } else {
-                ghost(ip, P.fbc[f], w, nx, ny, wj);
-            }
-            double dx = P.cf_dx[e], dy = P.cf_dy[e];
+            for (int m = 0; m < 4; m++) wj[k][m] = W[m * N + j];
+        }
 #pragma unroll
-            for (int k = 0; k < 4; k++) {
-                double d = wj[k] - w[k];
-                b1[k] += dx * d;
-                b2[k] += dy * d;
-                wmax[k] = fmax(wmax[k], wj[k]);
-                wmin[k] = fmin(wmin[k], wj[k]);
+        for (int k = 0; k < MAXV; k++) {
+            if ((E.flag[k] & CF_VALID) && E.nbr[k] < 0)   // nx, ny: the outward normal of a boundary face
+                ghost(ip, P.fbc[E.face[k]], w, nx.v[k], ny.v[k], wj[k]);
+            lc += (fabs(U * nx.v[k] + V * ny.v[k]) + cs) * S.v[k];
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                double d = wj[k][m] - w[m];
+                b1[m] += dx.v[k] * d;
+                b2[m] += dy.v[k] * d;
+                wmax[m] = fmax(wmax[m], wj[k][m]);
+                wmin[m] = fmin(wmin[m], wj[k][m]);
             }
         }
     };
@@ -1222,24 +1236,33 @@ __device__ __forceinline__ double gather_cell(const Params<T> &P, int c, int ins
 #pragma unroll
     for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
     double nuc = P.nu[c];
+    // all loads of a block before any is used (k_prep): an entry that does not
+    // exist reads the record of the cell's first face and counts with sign 0
+    // and length 0.  149 -> 98 us on 983k cells (SA), 0.5 GB at 5.4 TB/s; 36
+    // -> 28 us on 250k cells; held to 128 registers it spills: 130 us.
     auto block = [&](const Entries &E, int b) {
+        const Quad nx = quad4(P.enx, b), ny = quad4(P.eny, b), S = quad4(P.es, b);
+        double2 r[MAXV][FR_STRIDE / 2];
 #pragma unroll
         for (int k = 0; k < MAXV; k++) {
-            if (!(E.flag[k] & CF_VALID)) continue;
-            const int e = MAXV * b + k, f = E.face[k];
-            double sg = (E.flag[k] & CF_OWNER) ? 1.0 : -1.0;
-            const double *r = P.frec + FR_STRIDE * (size_t)f;
-            double g[4] = {r[FR_F0], r[FR_F1], r[FR_F2], r[FR_F3]};
-            if (E.nbr[k] < 0) wall_face_terms(P, ip, w, f, g);
+            const double2 *p = reinterpret_cast<const double2 *>(P.frec) + (FR_STRIDE / 2) * (size_t)E.face[k];
 #pragma unroll
-            for (int k = 0; k < 4; k++) m[k] -= sg * g[k];
-            double S = P.es[e];
-            ls += r[FR_LAM] * S;
+            for (int h = 0; h < FR_STRIDE / 2; h++) r[k][h] = p[h];
+        }
+#pragma unroll
+        for (int k = 0; k < MAXV; k++) {
+            const bool valid = E.flag[k] & CF_VALID;
+            const double sg = valid ? ((E.flag[k] & CF_OWNER) ? 1.0 : -1.0) : 0.0;
+            double g[4] = {r[k][FR_F0 / 2].x, r[k][FR_F0 / 2].y, r[k][FR_F2 / 2].x, r[k][FR_F2 / 2].y};
+            if (valid && E.nbr[k] < 0) wall_face_terms(P, ip, w, E.face[k], g);
+#pragma unroll
+            for (int m_ = 0; m_ < 4; m_++) m[m_] -= sg * g[m_];
+            ls += r[k][FR_LAM / 2].x * S.v[k];
             if (ip.sa) {
-                saR += sg * r[FR_SAF];
-                sagS += sg * r[FR_SAG];
-                double qc = (w[1] * P.enx[e] + w[2] * P.eny[e]) / w[0];   // the normal out of the cell
-                sad += 0.5 * (qc + fabs(qc)) * S + r[FR_SAK];
+                saR += sg * r[k][FR_SAF / 2].y;
+                sagS += sg * r[k][FR_SAG / 2].x;
+                double qc = (w[1] * nx.v[k] + w[2] * ny.v[k]) / w[0];   // the normal out of the cell
+                sad += 0.5 * (qc + fabs(qc)) * S.v[k] + (valid ? r[k][FR_SAK / 2].y : 0.0);
             }
         }
     };
