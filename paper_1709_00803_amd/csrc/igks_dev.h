@@ -162,14 +162,15 @@ constexpr int CHUNK_CELLS = 16;
 struct SweepGroups {
     int n;                              // groups
     int slots, waves;                   // LDS slots, waves per group
+    bool all_ring;                      // every group's increments fit the ring
     const int *cslot;                   // LDS slot of each cell, -1: the group's increments stay in global memory
     const int *ch_off;                  // group g's chunks: [ch_off[g], ch_off[g + 1])
     const int4 *chunk;                  // c0, c1, chunks of earlier (forward) and of later wavefronts
 };
 // LDS of a group's ring and its count of finished chunks
 constexpr size_t grp_lds(int slots, size_t size) { return 5 * size * (size_t)slots + 16; }
-// the whole forward or backward sweep, one launch; `update`: followed by the
-// update of every cell (after the last backward sweep)
+// the whole forward or backward sweep, one launch; `update`: the last backward
+// sweep, which also updates every cell
 template <typename T>
 void launch_sweep_grp(const Launch &L, const Params<T> &P, const SweepGroups &G, bool fwd, bool update);
 template <typename T> void launch_commit(const Launch &L, const Params<T> &P, int it);

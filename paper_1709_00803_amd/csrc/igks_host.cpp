@@ -54,6 +54,7 @@ struct Global {
     std::vector<int> ch_off, cslot;
     std::vector<int4> chunk;
     int grp_slots = 0, grp_waves = 4;
+    bool grp_all_ring = true;
     std::vector<int> coff;           // first global upload id of each instance
     std::vector<int> g2i;            // global upload id -> internal cell
     std::vector<int> cinst, finst, icell, ioff, ipos, cperm;
@@ -167,8 +168,8 @@ int launches_per_iteration(const igks_ctx *c, int sweep_mode)
 {
     const int nlev = std::max(1, c->g.nlev);
     // per-wavefront sweeps: forward steps of wavefronts 1 .. nlev-2, the last
-    // wavefront's two steps, backward steps of nlev-2 .. 0; the other
-    // schedules: forward, backward, update
+    // wavefront's two steps, backward steps of nlev-2 .. 0; the group sweeps:
+    // forward, backward, update (a bound: the update rides in the backward sweep)
     int sweeps = c->opt.scheme == 1 ? 1 : (sweep_mode >= 2 ? 3 : std::max(1, 2 * nlev - 2));
     if (c->opt.scheme != 1 && sweep_mode == 3 && two_block_passes(c)) sweeps += 2;   // the first pass
     return 5 + sweeps;   // prep, flux, gather, reduce, commit + the update / sweep launches
@@ -460,7 +461,7 @@ void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vecto
     for (int b = 0; b < ngb; b++) {
         need[b] = std::max(1, std::min(cells[b], span[b] + width[b]));
         if (grp_lds(need[b], size) <= cap) G.grp_slots = std::max(G.grp_slots, need[b]);
-        else need[b] = 0;
+        else { need[b] = 0; G.grp_all_ring = false; }
     }
     G.cslot.resize(N);
     for (int c = 0; c < N; c++) {
@@ -817,6 +818,7 @@ SweepGroups groups_of(igks_ctx *c)
     S.n = (int)c->g.ch_off.size() - 1;
     S.slots = c->g.grp_slots;
     S.waves = c->g.grp_waves;
+    S.all_ring = c->g.grp_all_ring;
     S.ch_off = (const int *)(c->ws + c->w.ch_off.off);
     S.cslot = (const int *)(c->ws + c->w.cslot.off);
     S.chunk = (const int4 *)(c->ws + c->w.chunk.off);

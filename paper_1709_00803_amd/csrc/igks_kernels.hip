@@ -388,6 +388,13 @@ __device__ __forceinline__ const double *cur_state(const Params<T> &P, int inst)
     return (P.is[inst].ncommit & 1) ? P.Wb : P.Wa;
 }
 
+// the other state buffer, which the update writes
+template <typename T>
+__device__ __forceinline__ double *next_state(const Params<T> &P, int inst)
+{
+    return (P.is[inst].ncommit & 1) ? P.Wa : P.Wb;
+}
+
 // ------------------------------------------------------- kinetic building blocks
 
 // <u^k>, k = 0..7, of the normalised Maxwellian exp(-lam (u-U)^2) on the
@@ -693,6 +700,20 @@ template <typename V>
 struct JacCoef {
     V nx, ny, m1, m2, ir, u, v, q, ke, ep;   // normal, momentum, 1/rho, velocity, V.n, |V|^2/2, rho E + p
 };
+// 1/x for the sweeps: in FP64 the refined hardware reciprocal (five
+// instructions; the divide's eleven were a tenth of what a wave of the group
+// sweep issues), in FP32 the divide.
+__device__ __forceinline__ double inv(double x) { return frcp(x); }
+__device__ __forceinline__ float inv(float x) { return 1.0f / x; }
+// Omega / dt_imp = Lambda_c / CFL (Eq.24), icfl = 1 / CFL used in FP64 only
+// (a product of its own, never fused into the diagonal's sum)
+__device__ __forceinline__ double over_cfl(double lamc, double, double icfl)
+{
+#pragma clang fp contract(off)
+    return lamc * icfl;
+}
+__device__ __forceinline__ float over_cfl(float lamc, float cfl, float) { return lamc / cfl; }
+
 template <typename V>
 __device__ __forceinline__ JacCoef<V> jac_coef(const V *W, V nx, V ny)
 {
@@ -700,7 +721,7 @@ __device__ __forceinline__ JacCoef<V> jac_coef(const V *W, V nx, V ny)
     JacCoef<V> c;
     const V r = W[0], E = W[3];
     c.nx = nx; c.ny = ny; c.m1 = W[1]; c.m2 = W[2];
-    c.ir = V(1) / r;
+    c.ir = inv(r);
     c.u = W[1] * c.ir; c.v = W[2] * c.ir;
     c.ke = V(0.5) * fma(c.u, c.u, c.v * c.v);
     c.ep = fma(V(GAMMA - 1.0), fma(-r, c.ke, E), E);
@@ -1659,7 +1680,7 @@ __device__ __forceinline__ void dinv_apply(const Params<T> &P, int c, const T *x
 template <typename T>
 struct SaDiag {
     T v;
-    __device__ __forceinline__ explicit SaDiag(T d) : v(std::is_same_v<T, double> ? T(1) / d : d) {}
+    __device__ __forceinline__ explicit SaDiag(T d) : v(std::is_same_v<T, double> ? inv(d) : d) {}
     __device__ __forceinline__ T solve(T a) const { return std::is_same_v<T, double> ? a * v : a / v; }
 };
 
@@ -1668,17 +1689,17 @@ struct SaDiag {
 // of sweep_cell with nothing subtracted, hence the same numbers).  Formed
 // where it is needed instead of in a launch of its own.
 template <typename T, bool ROE>
-__device__ __forceinline__ void first_front_incr(const Params<T> &P, const InstParam &ip, int j, T cfl, T *d)
+__device__ __forceinline__ void first_front_incr(const Params<T> &P, const InstParam &ip, int j, T cfl, T icfl, T *d)
 {
     const int N = P.nc;
-    const T odt = T(P.lamc[j]) / cfl;
+    const T odt = over_cfl(T(P.lamc[j]), cfl, icfl);
     if (ROE) {
         T m[4];
 #pragma unroll
         for (int k = 0; k < 4; k++) m[k] = T(P.M[k * N + j]);
         dinv_apply(P, j, m, d);
     } else {
-        const T iD = T(1) / (odt + T(P.lsum[j]));
+        const T iD = inv(odt + T(P.lsum[j]));
 #pragma unroll
         for (int k = 0; k < 4; k++) d[k] = T(P.M[k * N + j]) * iD;
     }
@@ -1723,7 +1744,10 @@ __device__ __forceinline__ TermCoef<T, ROE> term_coef(const Params<T> &P, bool s
     }
     if (sa) {
 #pragma clang fp contract(off)
-        const double qj = fma(wj[1], nx, wj[2] * ny) / wj[0];
+        const double mj = fma(wj[1], nx, wj[2] * ny);
+        double qj;
+        if constexpr (std::is_same_v<T, double>) qj = mj * C.jac.ir;
+        else qj = mj / wj[0];
         C.off = T(fma(-0.5 * (qj - fabs(qj)), S, sak));
     }
     return C;
@@ -1759,7 +1783,7 @@ __device__ __forceinline__ void term_apply(const TermCoef<T, ROE> &C, const T *d
 // wavefront, whose forward increments are not stored (first_front_incr).
 template <typename T, bool ROE>
 __device__ __forceinline__ void sweep_term(const Params<T> &P, const InstParam &ip, const double *W,
-                                           const double *w, int f, int e, int j, const T *dws, T cfl, int lev1,
+                                           const double *w, int f, int e, int j, const T *dws, T cfl, T icfl, int lev1,
                                            T *t)
 {
     const int N = P.nc;
@@ -1770,7 +1794,7 @@ __device__ __forceinline__ void sweep_term(const Params<T> &P, const InstParam &
 #pragma unroll
         for (int k = 0; k < 5; k++) wj[k] = W[k * N + j];
         if (j < lev1) {
-            first_front_incr<T, ROE>(P, ip, j, cfl, dj);
+            first_front_incr<T, ROE>(P, ip, j, cfl, icfl, dj);
         } else {
 #pragma unroll
             for (int k = 0; k < 5; k++) dj[k] = P.dW[k * N + j];
@@ -1791,10 +1815,10 @@ enum { SW_FWD = 0, SW_BWD = 1, SW_TOP = 2 };
 // clipped at 0; flags a non-physical result; returns the Eq.40 ratio
 // |dW| / |W| over the four flow variables.
 template <typename T>
-__device__ __forceinline__ double apply_update(const Params<T> &P, int c, int inst, const double *w, const double *d)
+__device__ __forceinline__ double apply_update(const Params<T> &P, int c, int inst, bool sa, double *Wn,
+                                               const double *w, const double *d)
 {
     const int N = P.nc;
-    double *Wn = (P.is[inst].ncommit & 1) ? P.Wa : P.Wb;
     double wn[4], num = 0.0, den = 0.0;
 #pragma unroll
     for (int k = 0; k < 4; k++) {
@@ -1804,7 +1828,7 @@ __device__ __forceinline__ double apply_update(const Params<T> &P, int c, int in
         Wn[k * N + c] = wn[k];
     }
     double tt = w[4];
-    if (P.ip[inst].sa) tt = fmax(tt + d[4], 0.0);
+    if (sa) tt = fmax(tt + d[4], 0.0);
     Wn[4 * N + c] = tt;
     double p = wn[3] - 0.5 * (wn[1] * wn[1] + wn[2] * wn[2]) / wn[0];
     if (!(wn[0] > 0.0) || !(p > 0.0) || !isfinite(tt) || !isfinite(p)) atomicOr(&P.is[inst].bad, 1);
@@ -1833,7 +1857,7 @@ __global__ __launch_bounds__(256) void k_explicit(Params<T> P)
 #pragma unroll
             for (int k = 0; k < 4; k++) d[k] = kc * P.M[k * N + c];
             d[4] = P.ip[inst].sa ? kc * P.M[4 * N + c] : 0.0;
-            e = apply_update(P, c, inst, w, d);
+            e = apply_update(P, c, inst, P.ip[inst].sa, next_state(P, inst), w, d);
         }
     }
     slot_update<false>(P.slot, SL_E40, inst, e);
@@ -1869,14 +1893,14 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
     const InstScalars &sc = P.is[inst];
     const InstParam &ip = P.ip[inst];
     const double *W = cur_state(P, inst);
-    const T cfl = T(sc.cfl);
+    const T cfl = T(sc.cfl), icfl = inv(cfl);
     double w[5];
 #pragma unroll
     for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
     const int f0 = P.cf_face[MAXV * c + q], j0 = P.cf_nbr[MAXV * c + q], fl0 = P.cf_flag[MAXV * c + q];
     const int nxt = quad_get<3>(fl0) >> CF_NEXT_SHIFT;
     const int ovf = nxt ? N + nxt - 1 : -1;   // a polygon's overflow block, or -1
-    const T odt = T(P.lamc[c]) / cfl;
+    const T odt = over_cfl(T(P.lamc[c]), cfl, icfl);
     const T D = odt + T(P.lsum[c]);
     T dws[5], acc[5], t[5];
     if (MODE == SW_FWD || MODE == SW_TOP) {
@@ -1886,7 +1910,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
             for (int m = 0; m < 5; m++) t[m] = T(0);
             if ((fl & CF_VALID) && j >= 0 && (fl & CF_LOWER))
-                sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, lev1, t);
+                sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, icfl, lev1, t);
 #pragma unroll
             for (int m = 0; m < 4; m++) acc[m] = quad_fold<true>(acc[m], t[m]);
             acc[4] = quad_fold<false>(acc[4], t[4]);
@@ -1897,7 +1921,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
         if (ROE) {
             dinv_apply(P, c, acc, dws);
         } else {
-            const T iD = T(1) / D;
+            const T iD = inv(D);
 #pragma unroll
             for (int k = 0; k < 4; k++) dws[k] = acc[k] * iD;
         }
@@ -1910,7 +1934,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
             return 0.0;
         }
     } else if (c < lev1) {
-        first_front_incr<T, ROE>(P, ip, c, cfl, dws);
+        first_front_incr<T, ROE>(P, ip, c, cfl, icfl, dws);
     } else {
 #pragma unroll
         for (int k = 0; k < 5; k++) dws[k] = P.dW[k * N + c];
@@ -1921,7 +1945,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
         for (int m = 0; m < 5; m++) t[m] = T(0);
         if ((fl & CF_VALID) && !(j >= 0 && (fl & (CF_LOWER | CF_OTHER))))
-            sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, lev1, t);
+            sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, icfl, lev1, t);
 #pragma unroll
         for (int m = 0; m < 5; m++) acc[m] = quad_fold<false>(acc[m], t[m]);
     };
@@ -1936,7 +1960,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
         for (int k = 0; k < 4; k++) d[k] = dws[k] - y[k];
     } else {
-        const T iD = T(1) / D;
+        const T iD = inv(D);
 #pragma unroll
         for (int k = 0; k < 4; k++) d[k] = dws[k] - acc[k] * iD;
     }
@@ -1946,7 +1970,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
     double dd[5];
 #pragma unroll
     for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
-    return apply_update(P, c, inst, w, dd);
+    return apply_update(P, c, inst, ip.sa, next_state(P, inst), w, dd);
 }
 
 // One wave per instance (block i): the L2 norms from the partial sums (in
@@ -2036,9 +2060,28 @@ __global__ __launch_bounds__(256) void k_sweep(Params<T> P, int c0, int c1, int 
 // most of the rest.
 //
 // The terms and their order are those of sweep_quad, so the iterates are
-// bitwise those of the launch-per-wavefront schedule.  The backward sweep
-// leaves the update (Eq.17, Eq.40) to one parallel pass afterwards (k_update).
+// bitwise those of the launch-per-wavefront schedule.  The last backward sweep
+// also updates the state (Eq.17, Eq.40), after the chunk is counted.
 constexpr unsigned SPIN_LIMIT = 1u << 22;
+
+// sweep kinds of the group sweep: forward; forward of a second block pass
+// (cross-block terms from the first); backward; backward with the update
+enum { GRP_FWD = 0, GRP_FWD2 = 1, GRP_BWD = 2, GRP_BWD_UPDATE = 3 };
+constexpr bool grp_fwd(int kind) { return kind <= GRP_FWD2; }
+
+// Element at byte offset `off` of an array whose address is the same on all
+// lanes: the offset is 32 bits (arrays of up to 2^29 doubles), so the load
+// needs no 64-bit address arithmetic on the lanes.
+template <typename V>
+__device__ __forceinline__ V at(const V *base, unsigned off)
+{
+    return *reinterpret_cast<const V *>(reinterpret_cast<const char *>(base) + off);
+}
+template <typename V>
+__device__ __forceinline__ void put(V *base, unsigned off, V v)
+{
+    *reinterpret_cast<V *>(reinterpret_cast<char *>(base) + off) = v;
+}
 
 // A chunk's cells [x, y) and the chunks that must be complete before it in
 // the forward (z) and the backward sweep (w); y <= x past the group's end.
@@ -2056,98 +2099,128 @@ __device__ __forceinline__ int4 chunk_place(const int4 *chunk, int i, int n)
     if (i >= n) m.y = -1;
     return m;
 }
-// a lane's cell and entry
+// a lane's cell and entry: the chunk's first cell, the lane's place after it
 struct ChunkIdx {
-    int need, c, e, f, j, fl;
+    int need, c0, f, j, fl;
+    int dc;     // cell - c0
     bool act;   // the lane has a cell
 };
 enum { SRC_NONE = 0, SRC_NEAR = 1, SRC_CROSS = 2, SRC_GHOST = 3 };
 // what a lane loads for its entry and its cell
-template <typename T, bool FWD, bool TWO, bool ROE>
+template <typename T, int KIND, bool ROE>
 struct ChunkRaw {
+    static constexpr bool FWD = grp_fwd(KIND);
+    static constexpr bool OWN = ROE || KIND == GRP_BWD_UPDATE;   // the cell's own state is needed
     using Rhs = std::conditional_t<FWD, double, T>;   // M, or the forward sweep's increment
     int src, bc, slot_c, slot_j, ovf;   // src: SRC_*
     double w[5], nx, ny, S, lam, sak, lamc, lsum, sadiag;
     Rhs rhs[5];
-    T dx[TWO ? 5 : 1];        // a first block pass's increment of the neighbour
-    double wc[ROE ? 5 : 1];   // Roe operator: the cell's own state,
-    T di[ROE ? 4 : 1];        // row q of its inverted diagonal block
+    T dx[KIND == GRP_FWD2 ? 5 : 1];   // a first block pass's increment of the neighbour
+    double wc[OWN ? 5 : 1];
+    T di[ROE ? 4 : 1];                // row q of the cell's inverted diagonal block
+};
+// what the chunks of a group share
+template <typename T>
+struct GroupRun {
+    const double *W;
+    double *Wn;        // the state the update writes
+    const int *cslot;
+    const int4 *chunk;
+    T *dw;             // the ring
+    unsigned *done;    // finished chunks
+    T cfl, icfl;
+    int n, q, cell, nw, inst;
 };
 
 template <typename T, bool FWD>
-__device__ __forceinline__ ChunkIdx chunk_entries(const Params<T> &P, const int4 &m, int q, int cell)
+__device__ __forceinline__ ChunkIdx chunk_entries(const Params<T> &P, const GroupRun<T> &G, const int4 &m)
 {
     ChunkIdx I;
-    I.act = m.x + cell < m.y;
-    I.need = FWD ? m.z : m.w;
-    I.c = min(m.x + cell, P.nc - 1);
-    I.e = MAXV * I.c + q;
-    I.f = P.cf_face[I.e];
-    I.j = P.cf_nbr[I.e];
-    I.fl = P.cf_flag[I.e];
+    I.c0 = __builtin_amdgcn_readfirstlane(m.x);
+    I.act = m.x + G.cell < m.y;
+    I.need = __builtin_amdgcn_readfirstlane(FWD ? m.z : m.w);
+    I.dc = min(G.cell, P.nc - 1 - I.c0);
+    const unsigned e = 4u * (unsigned)(MAXV * I.dc + G.q);
+    const size_t e0 = (size_t)MAXV * I.c0;
+    I.f = at(P.cf_face + e0, e);
+    I.j = at(P.cf_nbr + e0, e);
+    I.fl = at(P.cf_flag + e0, e);
     return I;
 }
 // which term an entry has in this sweep
-template <bool FWD, bool TWO>
+template <int KIND>
 __device__ __forceinline__ int entry_source(int j, int fl)
 {
     if (!(fl & CF_VALID)) return SRC_NONE;
-    if (FWD) {
+    if (grp_fwd(KIND)) {
         if (j < 0) return SRC_NONE;
         if (fl & CF_LOWER) return SRC_NEAR;
-        return ((fl & CF_OTHER) && TWO) ? SRC_CROSS : SRC_NONE;
+        return ((fl & CF_OTHER) && KIND == GRP_FWD2) ? SRC_CROSS : SRC_NONE;
     }
     if (j < 0) return SRC_GHOST;
     return (fl & (CF_LOWER | CF_OTHER)) ? SRC_NONE : SRC_NEAR;
 }
-// the loads of one entry's term (a ghost's state follows from the cell's)
-template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
-__device__ __forceinline__ void entry_gather(const Params<T> &P, const double *W, const int *cslot, int c, int e,
-                                             int f, int j, int fl, ChunkRaw<T, FWD, TWO, ROE> &R)
+// the loads of one entry's term, its geometry at element e of the arrays from
+// e0 on (a ghost's state follows from the cell's)
+template <typename T, int KIND, bool RING, bool ROE>
+__device__ __forceinline__ void entry_gather(const Params<T> &P, const GroupRun<T> &G, int c, size_t e0, unsigned e,
+                                             int f, int j, int fl, ChunkRaw<T, KIND, ROE> &R)
 {
-    const int N = P.nc, jw = j >= 0 ? j : c;
-    R.src = entry_source<FWD, TWO>(j, fl);
+    const size_t N = P.nc;
+    R.src = entry_source<KIND>(j, fl);
+    // an entry without a term here loads the cell's own data and one face for
+    // all such lanes: the lanes' distinct cache lines are what the loads cost
+    // where several groups share a CU
+    const int jw = R.src == SRC_NEAR || R.src == SRC_CROSS ? j : c;
+    const int fw = R.src != SRC_NONE ? f : __builtin_amdgcn_readfirstlane(f);
+    const unsigned oj = 8u * (unsigned)jw, of = 8u * (unsigned)fw, oe = 8u * e;
 #pragma unroll
-    for (int k = 0; k < 5; k++) R.w[k] = W[k * N + jw];
-    R.nx = P.enx[e]; R.ny = P.eny[e]; R.S = P.es[e];
-    R.lam = P.flam[f];
-    R.sak = P.fsak[f];
-    R.bc = P.fbc[f];
-    R.slot_j = RING ? cslot[jw] : jw;
-    if constexpr (TWO) {
+    for (int k = 0; k < 5; k++) R.w[k] = at(G.W + k * N, oj);
+    R.nx = at(P.enx + e0, oe); R.ny = at(P.eny + e0, oe); R.S = at(P.es + e0, oe);
+    R.lam = at(P.flam, of);
+    R.sak = at(P.fsak, of);
+    R.bc = grp_fwd(KIND) ? 0 : at(P.fbc, of / 2);
+    R.slot_j = RING ? at(G.cslot, oj / 2) : jw;
+    if constexpr (KIND == GRP_FWD2) {
 #pragma unroll
-        for (int k = 0; k < 5; k++) R.dx[k] = P.dWx[k * N + jw];
+        for (int k = 0; k < 5; k++) R.dx[k] = at(P.dWx + k * N, (unsigned)sizeof(T) * (unsigned)jw);
     }
 }
-template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
-__device__ __forceinline__ void chunk_gather(const Params<T> &P, const double *W, const int *cslot, int q,
-                                             const ChunkIdx &I, ChunkRaw<T, FWD, TWO, ROE> &R)
+template <typename T, int KIND, bool RING, bool ROE>
+__device__ __forceinline__ void chunk_gather(const Params<T> &P, const GroupRun<T> &G, const ChunkIdx &I,
+                                             ChunkRaw<T, KIND, ROE> &R)
 {
-    const int N = P.nc, c = I.c;
-    entry_gather<T, FWD, TWO, RING, ROE>(P, W, cslot, c, I.e, I.f, I.j, I.fl, R);
+    const size_t N = P.nc;
+    const int q = G.q;
+    entry_gather<T, KIND, RING, ROE>(P, G, I.c0 + I.dc, (size_t)MAXV * I.c0, (unsigned)(MAXV * I.dc + q), I.f, I.j,
+                                     I.fl, R);
     if (!I.act) R.src = SRC_NONE;
     const int nxt = quad_get<3>(I.fl) >> CF_NEXT_SHIFT;
-    R.ovf = I.act && nxt ? N + nxt - 1 : -1;   // a polygon's overflow block, or -1
-    R.slot_c = cslot[c];
-    R.lamc = P.lamc[c]; R.lsum = P.lsum[c]; R.sadiag = P.sadiag[c];
+    R.ovf = I.act && nxt ? P.nc + nxt - 1 : -1;   // a polygon's overflow block, or -1
+    const unsigned o = 8u * (unsigned)I.dc, ot = (unsigned)sizeof(T) * (unsigned)I.dc;
+    R.slot_c = at(G.cslot + I.c0, o / 2);
+    R.lamc = at(P.lamc + I.c0, o); R.lsum = at(P.lsum + I.c0, o); R.sadiag = at(P.sadiag + I.c0, o);
 #pragma unroll
     for (int k = 0; k < 5; k++) {
-        if constexpr (FWD) R.rhs[k] = P.M[k * N + c];
-        else R.rhs[k] = P.dW[k * N + c];
+        if constexpr (grp_fwd(KIND)) R.rhs[k] = at(P.M + k * N + I.c0, o);
+        else R.rhs[k] = at(P.dW + k * N + I.c0, ot);
+    }
+    if constexpr (ChunkRaw<T, KIND, ROE>::OWN) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) R.wc[k] = at(G.W + k * N + I.c0, o);
     }
     if constexpr (ROE) {
+        const T *di = P.dinv + (size_t)(4 * q) * N + I.c0 + I.dc;
 #pragma unroll
-        for (int k = 0; k < 5; k++) R.wc[k] = W[k * N + c];
-#pragma unroll
-        for (int k = 0; k < 4; k++) R.di[k] = P.dinv[(4 * q + k) * N + c];
+        for (int k = 0; k < 4; k++) R.di[k] = di[k * N];
     }
 }
-template <typename T, bool FWD, bool TWO, bool ROE>
+template <typename T, int KIND, bool ROE>
 __device__ __forceinline__ TermCoef<T, ROE> entry_coef(const Params<T> &P, const InstParam &ip,
-                                                       const ChunkRaw<T, FWD, TWO, ROE> &R)
+                                                       const ChunkRaw<T, KIND, ROE> &R)
 {
     double g[5] = {R.w[0], R.w[1], R.w[2], R.w[3], R.w[4]};
-    if (!FWD && R.src == SRC_GHOST) ghost(ip, R.bc, R.w, R.nx, R.ny, g);
+    if (!grp_fwd(KIND) && R.src == SRC_GHOST) ghost(ip, R.bc, R.w, R.nx, R.ny, g);
     const double *wc = R.w;
     if constexpr (ROE) wc = R.wc;
     return term_coef<T, ROE>(P, ip.sa, wc, g, R.nx, R.ny, R.S, R.lam, R.sak, R.src == SRC_CROSS);
@@ -2180,10 +2253,9 @@ __device__ __forceinline__ void no_term(TermCoef<T, ROE> &C, bool none)
     C.off = none ? T(0) : C.off;
 }
 // the neighbour's increment: from LDS, or without the ring from global memory
-template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
-__device__ __forceinline__ void entry_incr(const Params<T> &P, const ChunkRaw<T, FWD, TWO, ROE> &R, const T *dw, T *d)
+template <typename T, int KIND, bool RING, bool ROE>
+__device__ __forceinline__ void entry_incr(const Params<T> &P, const ChunkRaw<T, KIND, ROE> &R, const T *dw, T *d)
 {
-    const int N = P.nc;
     if constexpr (RING) {
 #pragma unroll
         for (int k = 0; k < 5; k++) d[k] = dw[5 * R.slot_j + k];
@@ -2192,52 +2264,43 @@ __device__ __forceinline__ void entry_incr(const Params<T> &P, const ChunkRaw<T,
         for (int k = 0; k < 5; k++) d[k] = T(0);
         if (R.src == SRC_NEAR) {
 #pragma unroll
-            for (int k = 0; k < 5; k++) d[k] = P.dW[k * N + R.slot_j];
+            for (int k = 0; k < 5; k++) d[k] = P.dW[(size_t)k * P.nc + R.slot_j];
         }
     }
 }
 // the term: with that increment, that of the first block pass, or the ghost's
-// from the cell's own
-template <typename T, bool FWD, bool TWO, bool ROE>
-__device__ __forceinline__ void entry_term(const InstParam &ip, const ChunkRaw<T, FWD, TWO, ROE> &R,
-                                           const TermCoef<T, ROE> &C, const T *dws, T *d, T *t)
+// (wall speed vw) from the cell's own
+template <typename T, int KIND, bool ROE>
+__device__ __forceinline__ void entry_term(const ChunkRaw<T, KIND, ROE> &R, const TermCoef<T, ROE> &C, const T *dws,
+                                           T vw, T *d, T *t)
 {
-    if constexpr (TWO) {
+    if constexpr (KIND == GRP_FWD2) {
 #pragma unroll
         for (int k = 0; k < 5; k++) d[k] = R.src == SRC_CROSS ? R.dx[k] : d[k];
     }
-    if (!FWD && R.src == SRC_GHOST)
-        ghost_incr<T>(R.bc, dws, T(R.nx), T(R.ny), T(wall_speed(ip, R.nx, R.ny)), d);
+    if (!grp_fwd(KIND) && R.src == SRC_GHOST) ghost_incr<T>(R.bc, dws, C.jac.nx, C.jac.ny, vw, d);
     term_apply<T, ROE>(C, d, t);
 }
 
-// what the chunks of a group share
-template <typename T>
-struct GroupRun {
-    const double *W;
-    const int *cslot;
-    const int4 *chunk;
-    T *dw;             // the ring
-    unsigned *done;    // finished chunks
-    T cfl;
-    int n, q, cell, nw, inst;
-};
 // Chunk i of the wave (loaded: A): the next chunk's loads into Rn (entries
 // In), the entries of the one after it into I, its place in `place`; this
-// chunk's coefficients; then the chunk itself.
-template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
-__device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam &ip, const GroupRun<T> &G, int i,
-                                            const ChunkRaw<T, FWD, TWO, ROE> &A, ChunkIdx &I,
-                                            ChunkRaw<T, FWD, TWO, ROE> &Rn, const ChunkIdx &In, int4 &place)
+// chunk's coefficients; then the chunk itself.  Returns the Eq.40 ratio of
+// the lane's cell where the sweep updates it.
+template <typename T, int KIND, bool RING, bool ROE>
+__device__ __forceinline__ double group_chunk(const Params<T> &P, const InstParam &ip, const GroupRun<T> &G, int i,
+                                              const ChunkRaw<T, KIND, ROE> &A, ChunkIdx &I,
+                                              ChunkRaw<T, KIND, ROE> &Rn, const ChunkIdx &In, int4 &place)
 {
-    const int N = P.nc, q = G.q;
+    constexpr bool FWD = grp_fwd(KIND);
+    const size_t N = P.nc;
+    const int q = G.q;
     const bool sa = ip.sa;
-    const int c = I.c, need = __builtin_amdgcn_readfirstlane(I.need);
+    const int c0 = I.c0, dc = I.dc, need = I.need;
     const bool store = q == 0 && I.act;
-    chunk_gather<T, FWD, TWO, RING, ROE>(P, G.W, G.cslot, q, In, Rn);
-    I = chunk_entries<T, FWD>(P, place, q, G.cell);
+    chunk_gather<T, KIND, RING, ROE>(P, G, In, Rn);
+    I = chunk_entries<T, FWD>(P, G, place);
     place = chunk_place<FWD>(G.chunk, i + 3 * G.nw, G.n);
-    TermCoef<T, ROE> C = entry_coef<T, FWD, TWO, ROE>(P, ip, A);
+    TermCoef<T, ROE> C = entry_coef<T, KIND, ROE>(P, ip, A);
     no_term(C, A.src == SRC_NONE);
     pin_coef(C);
     T rhs[5];
@@ -2246,27 +2309,32 @@ __device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam 
         rhs[k] = T(A.rhs[k]);
         pin(rhs[k]);
     }
-    const T odt = T(A.lamc) / G.cfl;
-    T iD = T(1) / (odt + T(A.lsum));
+    const T odt = over_cfl(T(A.lamc), G.cfl, G.icfl);
+    T iD = inv(odt + T(A.lsum));
     SaDiag<T> Ds(sa ? odt + T(A.sadiag) : T(1));
     pin(iD);
     pin(Ds.v);
+    T vw = T(0), vwB = T(0);
+    if (!FWD && A.src == SRC_GHOST && A.bc == BC_MOVING_WALL) vw = T(wall_speed(ip, A.nx, A.ny));
+    pin(vw);
     // the entries of polygons beyond the fourth, formed ahead too unless the
     // Roe matrices take the registers
-    ChunkRaw<T, FWD, TWO, ROE> B;
+    ChunkRaw<T, KIND, ROE> B;
     TermCoef<T, ROE> CB;
     const bool poly = __any(A.ovf >= 0);
     auto overflow = [&]() {
-        const int b = A.ovf >= 0 ? A.ovf : c, e = MAXV * b + q;
+        const int c = c0 + dc, b = A.ovf >= 0 ? A.ovf : c;
+        const size_t e = (size_t)MAXV * b + q;
         if constexpr (ROE) {
 #pragma unroll
             for (int k = 0; k < 5; k++) B.wc[k] = A.wc[k];
         }
-        entry_gather<T, FWD, TWO, RING, ROE>(P, G.W, G.cslot, c, e, P.cf_face[e], P.cf_nbr[e], P.cf_flag[e], B);
+        entry_gather<T, KIND, RING, ROE>(P, G, c, e, 0u, P.cf_face[e], P.cf_nbr[e], P.cf_flag[e], B);
         if (A.ovf < 0) B.src = SRC_NONE;
-        CB = entry_coef<T, FWD, TWO, ROE>(P, ip, B);
+        CB = entry_coef<T, KIND, ROE>(P, ip, B);
         no_term(CB, B.src == SRC_NONE);
         pin_coef(CB);
+        if (!FWD && B.src == SRC_GHOST && B.bc == BC_MOVING_WALL) vwB = T(wall_speed(ip, B.nx, B.ny));
     };
     if (!ROE && poly) overflow();
     // its turn: every chunk of the earlier wavefronts is complete.  The LDS
@@ -2288,7 +2356,7 @@ __device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam 
         done = __hip_atomic_load(G.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         if constexpr (RING) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            entry_incr<T, FWD, TWO, RING, ROE>(P, A, G.dw, d);
+            entry_incr<T, KIND, RING, ROE>(P, A, G.dw, d);
 #pragma unroll
             for (int k = 0; k < 5; k++) pin(d[k]);
         }
@@ -2296,9 +2364,9 @@ __device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam 
     __builtin_amdgcn_s_setprio(3);   // the others wait for this wave
     if constexpr (!RING) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        entry_incr<T, FWD, TWO, RING, ROE>(P, A, G.dw, d);
+        entry_incr<T, KIND, RING, ROE>(P, A, G.dw, d);
     }
-    entry_term<T, FWD, TWO, ROE>(ip, A, C, rhs, d, t);
+    entry_term<T, KIND, ROE>(A, C, rhs, vw, d, t);
     if (FWD) {
         // M less the lower neighbours' terms
 #pragma unroll
@@ -2310,8 +2378,8 @@ __device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam 
     }
     if (poly) {
         if (ROE) overflow();
-        entry_incr<T, FWD, TWO, RING, ROE>(P, B, G.dw, d);
-        entry_term<T, FWD, TWO, ROE>(ip, B, CB, rhs, d, t);
+        entry_incr<T, KIND, RING, ROE>(P, B, G.dw, d);
+        entry_term<T, KIND, ROE>(B, CB, rhs, vwB, d, t);
 #pragma unroll
         for (int m = 0; m < 4; m++) acc[m] = quad_fold<FWD>(acc[m], t[m]);
         acc[4] = quad_fold<false>(acc[4], t[4]);
@@ -2330,11 +2398,12 @@ __device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam 
     }
     if (FWD) d[4] = sa ? Ds.solve(acc[4]) : T(0);
     else d[4] = sa ? acc_add(rhs[4], Ds.solve(acc[4])) : T(0);
+    const unsigned ot = (unsigned)sizeof(T) * (unsigned)dc;
     if (store) {
 #pragma unroll
         for (int k = 0; k < 5; k++) {
             if (RING) G.dw[5 * A.slot_c + k] = d[k];
-            else P.dW[k * N + c] = d[k];
+            else put(P.dW + k * N + c0, ot, d[k]);
         }
     }
     if (RING) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -2344,35 +2413,49 @@ __device__ __forceinline__ void group_chunk(const Params<T> &P, const InstParam 
         if (spin >= SPIN_LIMIT) atomicOr(&P.is[G.inst].bad, 1);
     }
     __builtin_amdgcn_s_setprio(1);
-    if (RING && store) {
+    double e40 = 0.0;
+    if constexpr (KIND == GRP_BWD_UPDATE) {
+        // the final increments: nothing reads them from memory any more
+        if (store) {
+            double dd[5];
 #pragma unroll
-        for (int k = 0; k < 5; k++) P.dW[k * N + c] = d[k];
+            for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
+            e40 = apply_update(P, c0 + dc, G.inst, sa, G.Wn, A.wc, dd);
+        }
+    } else if (RING && store) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) put(P.dW + k * N + c0, ot, d[k]);
     }
+    return e40;
 }
-// The wave's chunks, two sets of registers in turn.
-template <typename T, bool FWD, bool TWO, bool RING, bool ROE>
-__device__ __forceinline__ void group_sweep(const Params<T> &P, const InstParam &ip, const GroupRun<T> &G, int wave)
+// The wave's chunks, two sets of registers in turn; the largest Eq.40 ratio
+// of the lane's cells.
+template <typename T, int KIND, bool RING, bool ROE>
+__device__ __forceinline__ double group_sweep(const Params<T> &P, const InstParam &ip, const GroupRun<T> &G, int wave)
 {
-    ChunkIdx I0 = chunk_entries<T, FWD>(P, chunk_place<FWD>(G.chunk, wave, G.n), G.q, G.cell);
-    ChunkIdx I1 = chunk_entries<T, FWD>(P, chunk_place<FWD>(G.chunk, wave + G.nw, G.n), G.q, G.cell);
+    constexpr bool FWD = grp_fwd(KIND);
+    const int4 p0 = chunk_place<FWD>(G.chunk, wave, G.n), p1 = chunk_place<FWD>(G.chunk, wave + G.nw, G.n);
     int4 place = chunk_place<FWD>(G.chunk, wave + 2 * G.nw, G.n);
-    ChunkRaw<T, FWD, TWO, ROE> R0, R1;
-    chunk_gather<T, FWD, TWO, RING, ROE>(P, G.W, G.cslot, G.q, I0, R0);
+    ChunkIdx I0 = chunk_entries<T, FWD>(P, G, p0), I1 = chunk_entries<T, FWD>(P, G, p1);
+    ChunkRaw<T, KIND, ROE> R0, R1;
+    chunk_gather<T, KIND, RING, ROE>(P, G, I0, R0);
+    double e = 0.0;
     for (int i = wave; i < G.n; i += 2 * G.nw) {
-        group_chunk<T, FWD, TWO, RING, ROE>(P, ip, G, i, R0, I0, R1, I1, place);
+        e = fmax(e, group_chunk<T, KIND, RING, ROE>(P, ip, G, i, R0, I0, R1, I1, place));
         if (i + G.nw >= G.n) break;
-        group_chunk<T, FWD, TWO, RING, ROE>(P, ip, G, i + G.nw, R1, I1, R0, I0, place);
+        e = fmax(e, group_chunk<T, KIND, RING, ROE>(P, ip, G, i + G.nw, R1, I1, R0, I0, place));
     }
+    return e;
 }
 
 // cslot: LDS slot of each cell, negative in a group whose couplings span more
 // cells than the ring holds: its increments pass through global memory
-// instead.  chunk[ch_off[g] .. ch_off[g + 1]): the group's chunks in forward
-// order.  Dynamic LDS: the ring of `slots` increments, then the count of
-// finished chunks.  TWO: the forward sweep of a second block pass.
-template <typename T, bool FWD, bool TWO, bool ONE, bool ROE>
+// instead (all_ring: no such group).  chunk[ch_off[g] .. ch_off[g + 1]): the
+// group's chunks in forward order.  Dynamic LDS: the ring of `slots`
+// increments, then the count of finished chunks.
+template <typename T, int KIND, bool ONE, bool ROE>
 __global__ __launch_bounds__(512) void k_sweep_grp(Params<T> P, const int *cslot, const int *ch_off,
-                                                   const int4 *chunk, int slots)
+                                                   const int4 *chunk, int slots, int all_ring)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     GroupRun<T> G;
@@ -2383,13 +2466,14 @@ __global__ __launch_bounds__(512) void k_sweep_grp(Params<T> P, const int *cslot
     if (G.n <= 0) return;
     G.chunk = chunk + k0;
     G.cslot = cslot;
-    const int c0 = G.chunk[0].x;
     // a group's cells belong to one instance
-    G.inst = ONE ? 0 : __builtin_amdgcn_readfirstlane(cell_inst(P, c0));
+    G.inst = ONE ? 0 : __builtin_amdgcn_readfirstlane(cell_inst(P, G.chunk[0].x));
     if (!ONE && P.is[G.inst].halt) return;   // the whole workgroup
     const InstParam ip = P.ip[G.inst];
     G.W = cur_state(P, G.inst);
+    G.Wn = next_state(P, G.inst);
     G.cfl = T(P.is[G.inst].cfl);
+    G.icfl = inv(G.cfl);
     const int lane = (int)threadIdx.x & 63;
     G.q = lane & 3;
     G.cell = lane >> 2;
@@ -2398,33 +2482,12 @@ __global__ __launch_bounds__(512) void k_sweep_grp(Params<T> P, const int *cslot
     if (threadIdx.x == 0) *G.done = 0u;
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (__builtin_amdgcn_readfirstlane(cslot[c0]) >= 0) group_sweep<T, FWD, TWO, true, ROE>(P, ip, G, wave);
-    else group_sweep<T, FWD, TWO, false, ROE>(P, ip, G, wave);
-}
-
-// W^{n+1} = W^n + dW for every cell from the finished backward sweep (the
-// same arithmetic as the fused update of the per-wavefront path)
-template <typename T, bool ONE>
-__global__ __launch_bounds__(256) void k_update(Params<T> P)
-{
-    const int N = P.nc;
-    int c = xcd_block() * blockDim.x + threadIdx.x;
-    int inst = -1;
-    double e = 0.0;
-    if (c < N) {
-        inst = live_inst<ONE>(P, P.cinst, c);
-        if (inst >= 0) {
-            const double *W = cur_state(P, inst);
-            double w[5], d[5];
-#pragma unroll
-            for (int k = 0; k < 5; k++) {
-                w[k] = W[k * N + c];
-                d[k] = double(P.dW[k * N + c]);
-            }
-            e = apply_update(P, c, inst, w, d);
-        }
-    }
-    slot_update<false>(P.slot, SL_E40, inst, e);
+    double e;
+    if (all_ring || __builtin_amdgcn_readfirstlane(cslot[G.chunk[0].x]) >= 0)
+        e = group_sweep<T, KIND, true, ROE>(P, ip, G, wave);
+    else
+        e = group_sweep<T, KIND, false, ROE>(P, ip, G, wave);
+    if (KIND == GRP_BWD_UPDATE) slot_update<false>(P.slot, SL_E40, G.inst, e);
 }
 
 // exact distance from each centroid to the nearest wall segment of its instance
@@ -2533,14 +2596,14 @@ template <typename T> void launch_reduce(const Launch &L, const Params<T> &P, in
         else hipLaunchKernelGGL((K<T, X, false, true>), grid, block, 0, L.s, __VA_ARGS__);               \
     } while (0)
 
-template <typename T, bool FWD, bool TWO>
+template <typename T, int KIND>
 static void launch_grp(const Launch &L, const Params<T> &P, const SweepGroups &G)
 {
     const bool one = P.ninst == 1, roe = P.dinv != nullptr;
-    auto *k = one ? (roe ? k_sweep_grp<T, FWD, TWO, true, true> : k_sweep_grp<T, FWD, TWO, true, false>)
-                  : (roe ? k_sweep_grp<T, FWD, TWO, false, true> : k_sweep_grp<T, FWD, TWO, false, false>);
+    auto *k = one ? (roe ? k_sweep_grp<T, KIND, true, true> : k_sweep_grp<T, KIND, true, false>)
+                  : (roe ? k_sweep_grp<T, KIND, false, true> : k_sweep_grp<T, KIND, false, false>);
     hipLaunchKernelGGL(k, dim3(G.n), dim3(64 * G.waves), grp_lds(G.slots, sizeof(T)), L.s, P, G.cslot, G.ch_off,
-                       G.chunk, G.slots);
+                       G.chunk, G.slots, G.all_ring ? 1 : 0);
 }
 
 template <typename T> void launch_sweep(const Launch &L, const Params<T> &P, int c0, int c1, int mode, int lev1)
@@ -2555,10 +2618,10 @@ template <typename T>
 void launch_sweep_grp(const Launch &L, const Params<T> &P, const SweepGroups &G, bool fwd, bool update)
 {
     if (G.n <= 0) return;
-    if (!fwd) launch_grp<T, false, false>(L, P, G);
-    else if (P.dWx) launch_grp<T, true, true>(L, P, G);
-    else launch_grp<T, true, false>(L, P, G);
-    if (update) LAUNCH_ONE(k_update, T, dim3(nblk(P.nc, L.block[3])), dim3(L.block[3]), P);
+    if (!fwd && update) launch_grp<T, GRP_BWD_UPDATE>(L, P, G);
+    else if (!fwd) launch_grp<T, GRP_BWD>(L, P, G);
+    else if (P.dWx) launch_grp<T, GRP_FWD2>(L, P, G);
+    else launch_grp<T, GRP_FWD>(L, P, G);
 }
 template <typename T> void launch_roe_diag(const Launch &L, const Params<T> &P)
 {
