@@ -24,9 +24,10 @@ constexpr int CF_LOWER = 2;   // interior neighbour of the same sweep block with
 constexpr int CF_VALID = 4;   // the entry exists (triangles leave their fourth entry empty)
 constexpr int CF_OTHER = 16;  // interior neighbour in another sweep block (left out of the sweeps)
 // A polygon's faces and vertices beyond the fourth sit in an overflow block
-// of four more (block nc + o); the last entry of a block carries o + 1 in
-// the flag bits from CF_NEXT_SHIFT on (0: no further block).
-constexpr int CF_NEXT_SHIFT = 8;
+// of four more, block covf[c]; the last entry of its block has CF_POLY.
+constexpr int CF_POLY = 32;
+// from this bit on: the LDS slot of the neighbour's increment in the group sweep
+constexpr int CF_SLOT_SHIFT = 8;
 
 constexpr int MAXV = 4;       // entries and vertices per block (triangles pad by repeating a vertex)
 constexpr int MAXP = 8;       // vertices of the largest cell (two blocks)
@@ -39,6 +40,8 @@ constexpr int NSLOT = 64;
 constexpr int SLOT_STRIDE = 16;   // unsigned long longs from one slot to the next
 enum { SL_DTMIN = 0, SL_RESINF = 1, SL_E40 = 2, NSL = 3 };   // Eq.23 minimum, max |M|, Eq.40 maximum
 constexpr int NORM_SLICE = 1024;   // squares per block of the residual-norm partial sums
+// cell record layout (Params::crec)
+constexpr int CR_STRIDE = 8, CR_M = 0, CR_LSUM = 5, CR_SADIAG = 6, CR_LAMC = 7;
 // face record layout (Params::frec)
 constexpr int FR_STRIDE = 8, FR_F0 = 0, FR_F1 = 1, FR_LAM = 2, FR_SAF = 3, FR_F2 = 4, FR_F3 = 5, FR_SAG = 6, FR_SAK = 7;
 constexpr int NCLASS = 4;     // kernel classes with a tunable block size: prep, flux, gather, sweep
@@ -83,9 +86,12 @@ struct Params {
     double *lamc;              // Eq.21 spectral radius sum
     double *vort;              // |dV/dx - dU/dy| (unlimited gradients)
     double *nu;                // laminar kinematic viscosity
-    double *M;                 // residual: 4 flow components + SA right-hand side
-    double *lsum;              // 1/2 sum lambda S (Eq.20 diagonal)
-    double *sadiag;            // SA diagonal without Omega/dt
+    // nc x CR_STRIDE cell records, what the sweeps read of a cell in one 64-byte
+    // line: the residual (4 flow components, SA right-hand side), 1/2 sum
+    // lambda S (Eq.20 diagonal), the SA diagonal without Omega/dt, Lambda_c
+    double *crec;
+    T *srec;                   // the same shape from the forward to the backward group sweep:
+                               // dW*, 1 / D, the SA diagonal (in the gradients' memory)
     double *r2;                // squares for the norms, M_rho^2 then R_SA^2, at the cell's ipos
     T *dW;                     // LU-SGS increment, 5 x nc
     const T *dWx;              // a first block pass's increments, whose cross-block terms the
@@ -101,6 +107,7 @@ struct Params {
     // the overflow block of a polygon): face, neighbour (-1: ghost cell),
     // flags, centroid offsets to the neighbour (or ghost)
     const int *cf_face, *cf_nbr, *cf_flag;
+    const int *covf;           // overflow block of each polygon (of meshes that have any)
     const double *cf_dx, *cf_dy;
     // per entry, the face seen from the entry's cell: the normal pointing out
     // of the cell and the face length (a cell's entries are contiguous)
@@ -158,14 +165,16 @@ template <typename T> void launch_roe_diag(const Launch &L, const Params<T> &P);
 template <typename T> void launch_sweep(const Launch &L, const Params<T> &P, int c0, int c1, int mode, int lev1);
 // Groups of cells that the sweeps do not couple (sweep blocks; an instance
 // without blocks is one), each swept by one workgroup.
-constexpr int CHUNK_CELLS = 16;
+constexpr int CHUNK_CELLS = 16, CH_SLOT_SHIFT = 5;
+constexpr int GRP_WAVES = 12, GRP_WAVES_ROE = 8;   // at most (registers)
 struct SweepGroups {
     int n;                              // groups
     int slots, waves;                   // LDS slots, waves per group
     bool all_ring;                      // every group's increments fit the ring
-    const int *cslot;                   // LDS slot of each cell, -1: the group's increments stay in global memory
     const int *ch_off;                  // group g's chunks: [ch_off[g], ch_off[g + 1])
-    const int4 *chunk;                  // c0, c1, chunks of earlier (forward) and of later wavefronts
+    // per chunk: first cell; cells | (LDS slot of the first + 1) << CH_SLOT_SHIFT (slot -1: the
+    // group's increments stay in global memory); chunks of earlier (forward) and of later wavefronts
+    const int4 *chunk;
 };
 // LDS of a group's ring and its count of finished chunks
 constexpr size_t grp_lds(int slots, size_t size) { return 5 * size * (size_t)slots + 16; }
@@ -180,7 +189,8 @@ void launch_wall_distance(const Launch &L, int nc, const double *xc, const doubl
                           const int *woff, const double *wseg, double *dwall);
 void launch_gather_faces(const Launch &L, int n, const int *faces, const double *frec, int nf, double *out);
 void launch_fill_instance(const Launch &L, int n, const int *cells, int nc, const double *Winf, double *W);
-void launch_copy_instance(const Launch &L, int n, const int *cells, int nc, const double *src, double *dst,
+// component k of cell c of the internal array at k sk + c sc
+void launch_copy_instance(const Launch &L, int n, const int *cells, size_t sk, size_t sc, const double *src, double *dst,
                           bool to_instance);
 
 }  // namespace igks

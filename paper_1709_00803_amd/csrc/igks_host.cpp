@@ -50,8 +50,9 @@ struct Global {
     // instance without blocks is one).  Group g's chunks of at most
     // CHUNK_CELLS cells of one wavefront, in forward order, are
     // chunk[ch_off[g]] .. chunk[ch_off[g + 1] - 1]; cslot: a cell's slot in the
-    // ring of increments its group's sweep keeps in LDS
+    // ring of increments its group's sweep keeps in LDS (in the entries' flags)
     std::vector<int> ch_off, cslot;
+    std::vector<int> covf;           // overflow block of each cell, -1: none (empty: no polygons)
     std::vector<int4> chunk;
     int grp_slots = 0, grp_waves = 4;
     bool grp_all_ring = true;
@@ -76,11 +77,11 @@ struct Buf {
 constexpr int NKT = 6;
 
 struct WsMap {
-    Buf ip, is, slot, Wa, Wb, grad, lamc, vort, nu, M, lsum, sadiag, r2, dW, dW1, dinv, area, lsinv, dwall, vtx, phi;
+    Buf ip, is, slot, Wa, Wb, grad, lamc, vort, nu, crec, r2, dW, dW1, dinv, area, lsinv, dwall, vtx, phi;
     Buf cinst, finst, ioff, g2i, cf_face, cf_nbr, cf_flag, cf_dx, cf_dy;
     Buf fl, fr, fbc, fnx, fny, flen, frl, frr, fidl, fidr, firn, ipart, hist, ipos, cperm;
     Buf frec, flam, fsak, enx, eny, es;
-    Buf wall_faces, wall_out, woff, wseg, ch_off, cslot, chunk, stage, backup;
+    Buf wall_faces, wall_out, woff, wseg, ch_off, covf, chunk, stage, backup;
     size_t total;
 };
 
@@ -476,7 +477,8 @@ void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vecto
         for (auto &p : rng[b]) {
             const int before = (int)(G.chunk.size() - k0);
             for (int c0 = p.first; c0 < p.second; c0 += CHUNK_CELLS)
-                G.chunk.push_back(make_int4(c0, std::min(c0 + CHUNK_CELLS, p.second), before, 0));
+                G.chunk.push_back(make_int4(c0, std::min(CHUNK_CELLS, p.second - c0) |
+                                                    (G.cslot[c0] + 1) << CH_SLOT_SHIFT, before, 0));
         }
         for (size_t k = G.chunk.size(), later = 0; k > k0;) {
             // chunks of the wavefront that ends at k, all with the same count of later ones
@@ -491,13 +493,14 @@ void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vecto
     }
     // Four waves, one per SIMD, take turns where a wavefront is mostly one
     // chunk or where the groups fill the CUs; where few groups have wider
-    // wavefronts, eight run their chunks at once.  Forward + backward sweep in
-    // us with 4 / 8 waves: 64x32 plate, 21 blocks 38 / 38; 250k aerofoil, 523
-    // blocks of 1.8 chunks a wavefront, 254 / 260; 350k plate, 1367 blocks,
-    // 771 / 1189; in natural order the plate 132 / 110, the 100x100 cavity
-    // (3.6 chunks a wavefront) 522 / 364.
+    // wavefronts, twelve (three per SIMD, what the registers hold; eight with
+    // the Roe operator) run their chunks at once.  Forward + backward sweep in
+    // us with 4 / 8 / 12 waves: 64x32 plate, 21 blocks 36 / 36 / 37; 250k
+    // aerofoil, 523 blocks of 1.8 chunks a wavefront, 188 / 216 / 225; in natural
+    // order the plate 130 / 109 / 109, the polygon cavity 697 / 490 / 467, the
+    // 100x100 cavity (3.6 chunks a wavefront) 496 / 332 / 298.
     const double per_front = (double)G.chunk.size() / std::max<size_t>(1, nfronts);
-    G.grp_waves = per_front > 1.35 && ngb <= 256 ? 8 : 4;
+    G.grp_waves = per_front > 1.35 && ngb <= 256 ? 12 : 4;
 }
 
 // Concatenate the instances in the internal order: cells by (wavefront,
@@ -636,8 +639,7 @@ int combine(igks_ctx *ctx)
         const int u = gu[order[c]];
         if (m.cf_ptr[u + 1] - m.cf_ptr[u] > MAXV || m.cptr[u + 1] - m.cptr[u] > MAXV) ovf[c] = NB++;
     }
-    if (NB - N >= (1 << (31 - CF_NEXT_SHIFT)))
-        return fail(ctx, IGKS_EMESH, "too many cells with more than " + std::to_string(MAXV) + " faces");
+    if (NB > N) G.covf = ovf;
     G.NB = NB;
     G.vtx.resize(2 * MAXV * (size_t)NB);
     // entries: MAXV per block, in the order of the cell's faces; unused
@@ -678,14 +680,15 @@ int combine(igks_ctx *ctx)
             G.cf_nbr[e] = other >= 0 ? G.g2i[off + other] : -1;
             const bool coupled = other >= 0 && same_block(m, u, other);
             G.cf_flag[e] = CF_VALID | (own ? CF_OWNER : 0) | ((coupled && other < u) ? CF_LOWER : 0) |
-                           ((other >= 0 && !coupled) ? CF_OTHER : 0);
+                           ((other >= 0 && !coupled) ? CF_OTHER : 0) |
+                           (coupled ? std::max(0, G.cslot[G.g2i[off + other]]) << CF_SLOT_SHIFT : 0);
             G.cf_dx[e] = dx;
             G.cf_dy[e] = dy;
             a11 += dx * dx; a12 += dx * dy; a22 += dy * dy;
         }
         const int nslots = ovf[c] >= 0 ? 2 * MAXV : MAXV;
         for (int kk = nfc; kk < nslots; kk++) G.cf_face[slot(kk)] = G.cf_face[(size_t)MAXV * c];
-        if (ovf[c] >= 0) G.cf_flag[(size_t)MAXV * c + MAXV - 1] |= (ovf[c] - N + 1) << CF_NEXT_SHIFT;
+        if (ovf[c] >= 0) G.cf_flag[(size_t)MAXV * c + MAXV - 1] |= CF_POLY;
         double det = a11 * a22 - a12 * a12;
         if (!(det > 0))
             return fail(ctx, IGKS_EMESH, "instance " + std::to_string(i) + ": singular least-squares stencil at cell " +
@@ -732,8 +735,9 @@ WsMap layout(const Global &G, int ninst, const igks_options &o, int hist_cap)
     w.Wa = L.add(5 * N * D); w.Wb = L.add(5 * N * D);
     w.grad = L.add(8 * N * D); w.lamc = L.add(N * D); w.vort = L.add(N * D); w.nu = L.add(N * D);
     w.phi = L.add(4 * N * D);
-    w.M = L.add(5 * N * D); w.lsum = L.add(N * D); w.sadiag = L.add(N * D); w.r2 = L.add(2 * N * D);
+    w.crec = L.add(CR_STRIDE * N * D);
     w.dW = L.add(5 * N * (o.precision == IGKS_MIXED ? sizeof(float) : D));
+    w.r2 = Buf{w.dW.off, 2 * N * D};   // between the gather and the reduction, when no increment is held
     // the first pass's increments (two block passes)
     w.dW1 = L.add(o.block_passes == 2 ? 5 * N * (o.precision == IGKS_MIXED ? sizeof(float) : D) : 0);
     // the inverted 4x4 LU-SGS diagonal blocks (Roe-matrix operator)
@@ -758,7 +762,7 @@ WsMap layout(const Global &G, int ninst, const igks_options &o, int hist_cap)
     w.woff = L.add((NI + 1) * I);
     w.wseg = L.add(4 * NW * D);
     w.ch_off = L.add(G.ch_off.size() * I);
-    w.cslot = L.add(N * I);
+    w.covf = L.add(G.covf.size() * I);
     w.chunk = L.add(G.chunk.size() * sizeof(int4));
     w.stage = L.add(5 * (size_t)std::max(1, G.max_inst_cells) * D);
     w.backup = L.add(10 * N * D + NI * sizeof(InstScalars));
@@ -786,13 +790,14 @@ void fill_params(igks_ctx *c, Params<T> &P)
     P.is = (InstScalars *)(b + w.is.off);
     P.slot = (unsigned long long *)(b + w.slot.off);
     P.Wa = D(w.Wa); P.Wb = D(w.Wb); P.grad = D(w.grad); P.lamc = D(w.lamc); P.vort = D(w.vort); P.nu = D(w.nu);
-    P.M = D(w.M); P.lsum = D(w.lsum); P.sadiag = D(w.sadiag); P.r2 = D(w.r2); P.dW = (T *)(b + w.dW.off);
+    P.crec = D(w.crec); P.srec = (T *)(b + w.grad.off); P.r2 = D(w.r2); P.dW = (T *)(b + w.dW.off);
     P.dWx = nullptr;
     P.dinv = c->opt.lusgs_op >= 1 && c->opt.scheme == 0 ? (T *)(b + w.dinv.off) : nullptr;
     P.roe_kin = c->opt.lusgs_op == 2;
     P.area = D(w.area); P.lsinv = D(w.lsinv); P.dwall = D(w.dwall); P.vtx = D(w.vtx);
     P.nb = c->g.NB;
     P.cf_face = In(w.cf_face); P.cf_nbr = In(w.cf_nbr); P.cf_flag = In(w.cf_flag);
+    P.covf = In(w.covf);
     P.cf_dx = D(w.cf_dx); P.cf_dy = D(w.cf_dy);
     P.fl = In(w.fl); P.fr = In(w.fr); P.fbc = In(w.fbc);
     P.fnx = D(w.fnx); P.fny = D(w.fny); P.flen = D(w.flen); P.frl = D(w.frl); P.frr = D(w.frr);
@@ -820,7 +825,6 @@ SweepGroups groups_of(igks_ctx *c)
     S.waves = c->g.grp_waves;
     S.all_ring = c->g.grp_all_ring;
     S.ch_off = (const int *)(c->ws + c->w.ch_off.off);
-    S.cslot = (const int *)(c->ws + c->w.cslot.off);
     S.chunk = (const int4 *)(c->ws + c->w.chunk.off);
     return S;
 }
@@ -1348,7 +1352,7 @@ int igks_bind_workspace(igks_ctx *c, void *dptr, size_t bytes)
     rc |= up(w.woff, G.woff.data(), G.woff.size() * I);
     rc |= up(w.wseg, G.wseg.data(), G.wseg.size() * D);
     rc |= up(w.ch_off, G.ch_off.data(), G.ch_off.size() * I);
-    rc |= up(w.cslot, G.cslot.data(), N * I);
+    rc |= up(w.covf, G.covf.data(), G.covf.size() * I);
     rc |= up(w.chunk, G.chunk.data(), G.chunk.size() * sizeof(int4));
     // centroids for the wall distance, in the autotuner's backup area
     const Buf cx{w.backup.off, N * D}, cy{w.backup.off + N * D, N * D};
@@ -1510,7 +1514,7 @@ int igks_batch_get_state(igks_ctx *c, int32_t inst, double *W)
     if (!W) return IGKS_EINVAL;
     const int n = c->inst[inst].nc;
     Launch L = launch_of(c);
-    launch_copy_instance(L, n, inst_cells(c, inst), c->g.N, cur_buffer(c, inst), stage_buffer(c), false);
+    launch_copy_instance(L, n, inst_cells(c, inst), c->g.N, 1, cur_buffer(c, inst), stage_buffer(c), false);
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpyAsync(W, stage_buffer(c), sizeof(double) * 5 * n, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -1537,8 +1541,8 @@ int igks_batch_set_state(igks_ctx *c, int32_t inst, const double *W, const igks_
     HIPCHK(c, hipMemcpyAsync(stage_buffer(c), W, sizeof(double) * 5 * n, hipMemcpyHostToDevice, c->stream));
     Launch L = launch_of(c);
     launch_reset(L, c->P64, 1, inst);
-    launch_copy_instance(L, n, inst_cells(c, inst), c->g.N, stage_buffer(c), (s.ncommit & 1) ? c->P64.Wb : c->P64.Wa,
-                         true);
+    launch_copy_instance(L, n, inst_cells(c, inst), c->g.N, 1, stage_buffer(c),
+                         (s.ncommit & 1) ? c->P64.Wb : c->P64.Wa, true);
     HIPCHK(c, hipGetLastError());
     c->hist[inst].clear();
     return sync_scalars(c);
@@ -1583,7 +1587,7 @@ int igks_batch_compute_residual(igks_ctx *c, int32_t inst, double *M)
     if (rc) return rc;
     const int n = c->inst[inst].nc;
     Launch L = launch_of(c);
-    launch_copy_instance(L, n, inst_cells(c, inst), c->g.N, c->P64.M, stage_buffer(c), false);
+    launch_copy_instance(L, n, inst_cells(c, inst), 1, CR_STRIDE, c->P64.crec, stage_buffer(c), false);
     HIPCHK(c, hipGetLastError());
     if (M) HIPCHK(c, hipMemcpyAsync(M, stage_buffer(c), sizeof(double) * 5 * n, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -350,10 +350,9 @@ __device__ __forceinline__ Quad quad4(const double *a, int b)
 }
 // the block after E, or -1 (triangles and quadrilaterals have one block)
 template <typename T>
-__device__ __forceinline__ int next_block(const Params<T> &P, const Entries &E)
+__device__ __forceinline__ int next_block(const Params<T> &P, const Entries &E, int c)
 {
-    const int o = E.flag[MAXV - 1] >> CF_NEXT_SHIFT;
-    return o ? P.nc + o - 1 : -1;
+    return (E.flag[MAXV - 1] & CF_POLY) ? P.covf[c] : -1;
 }
 
 // instance of a cell / face (a one-instance context needs no lookup)
@@ -818,7 +817,7 @@ __device__ __forceinline__ double prep_cell(const Params<T> &P, int c, int inst)
     };
     const Entries E0 = entries(P, c);
     block(E0, c);
-    const int ovf = next_block(P, E0);   // a polygon's overflow block, or -1
+    const int ovf = next_block(P, E0, c);   // a polygon's overflow block, or -1
     if (ovf >= 0) block(entries(P, ovf), ovf);
     P.lamc[c] = lc;
     double L11 = P.lsinv[c], L12 = P.lsinv[N + c], L22 = P.lsinv[2 * N + c];
@@ -1306,7 +1305,7 @@ __device__ __forceinline__ double gather_cell(const Params<T> &P, int c, int ins
     double w[5];
 #pragma unroll
     for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
-    double nuc = P.nu[c];
+    const double nuc = P.nu[c], lamc = P.lamc[c];
     // all loads of a block before any is used (k_prep): an entry that does not
     // exist reads the record of the cell's first face and counts with sign 0
     // and length 0.  149 -> 98 us on 983k cells (SA), 0.5 GB at 5.4 TB/s; 36
@@ -1339,25 +1338,24 @@ __device__ __forceinline__ double gather_cell(const Params<T> &P, int c, int ins
     };
     const Entries E0 = entries(P, c);
     block(E0, c);
-    const int ovf = next_block(P, E0);
+    const int ovf = next_block(P, E0, c);
     if (ovf >= 0) block(entries(P, ovf), ovf);
-#pragma unroll
-    for (int k = 0; k < 4; k++) P.M[k * N + c] = m[k];
-    P.lsum[c] = 0.5 * ls;
     const int pos = P.ipos[c];
     P.r2[pos] = m[0] * m[0];
+    double rsa = 0.0, sdiag = 0.0;
     if (ip.sa) {
         double Sr, jd;
         sa_source(w[4], nuc, P.dwall[c], P.vort[c], Sr, jd);
         double a = P.area[c];
-        double rsa = saR - (SA_CB2 / SA_SIGMA) * w[4] * sagS + a * Sr;
-        P.M[4 * N + c] = rsa;
-        P.sadiag[c] = sad + a * jd;
-        P.r2[N + pos] = rsa * rsa;
-    } else {
-        P.M[4 * N + c] = 0.0;
-        P.r2[N + pos] = 0.0;
+        rsa = saR - (SA_CB2 / SA_SIGMA) * w[4] * sagS + a * Sr;
+        sdiag = sad + a * jd;
     }
+    P.r2[N + pos] = rsa * rsa;
+    double2 *rec = reinterpret_cast<double2 *>(P.crec + CR_STRIDE * (size_t)c);
+    rec[0] = make_double2(m[0], m[1]);
+    rec[1] = make_double2(m[2], m[3]);
+    rec[2] = make_double2(rsa, 0.5 * ls);
+    rec[3] = make_double2(sdiag, lamc);
     return fmax(fmax(fabs(m[0]), fabs(m[1])), fmax(fabs(m[2]), fabs(m[3])));
 }
 
@@ -1649,9 +1647,9 @@ __global__ __launch_bounds__(256) void k_roe_diag(Params<T> P)
     };
     const Entries E0 = entries(P, c);
     block(E0, c);
-    const int ovf = next_block(P, E0);
+    const int ovf = next_block(P, E0, c);
     if (ovf >= 0) block(entries(P, ovf), ovf);
-    const double dg = P.lamc[c] / P.is[inst].cfl + P.lsum[c];
+    const double dg = P.lamc[c] / P.is[inst].cfl + P.crec[CR_STRIDE * (size_t)c + CR_LSUM];
 #pragma unroll
     for (int r = 0; r < 4; r++) a[5 * r] += dg;
     double b[16];
@@ -1680,6 +1678,7 @@ __device__ __forceinline__ void dinv_apply(const Params<T> &P, int c, const T *x
 template <typename T>
 struct SaDiag {
     T v;
+    SaDiag() = default;
     __device__ __forceinline__ explicit SaDiag(T d) : v(std::is_same_v<T, double> ? inv(d) : d) {}
     __device__ __forceinline__ T solve(T a) const { return std::is_same_v<T, double> ? a * v : a / v; }
 };
@@ -1691,19 +1690,18 @@ struct SaDiag {
 template <typename T, bool ROE>
 __device__ __forceinline__ void first_front_incr(const Params<T> &P, const InstParam &ip, int j, T cfl, T icfl, T *d)
 {
-    const int N = P.nc;
-    const T odt = over_cfl(T(P.lamc[j]), cfl, icfl);
+    const double2 *rec = reinterpret_cast<const double2 *>(P.crec + CR_STRIDE * (size_t)j);
+    const double2 r0 = rec[0], r1 = rec[1], r2 = rec[2], r3 = rec[3];
+    const T odt = over_cfl(T(r3.y), cfl, icfl);
+    const T m[4] = {T(r0.x), T(r0.y), T(r1.x), T(r1.y)};
     if (ROE) {
-        T m[4];
-#pragma unroll
-        for (int k = 0; k < 4; k++) m[k] = T(P.M[k * N + j]);
         dinv_apply(P, j, m, d);
     } else {
-        const T iD = inv(odt + T(P.lsum[j]));
+        const T iD = inv(odt + T(r2.y));
 #pragma unroll
-        for (int k = 0; k < 4; k++) d[k] = T(P.M[k * N + j]) * iD;
+        for (int k = 0; k < 4; k++) d[k] = m[k] * iD;
     }
-    d[4] = ip.sa ? SaDiag<T>(odt + T(P.sadiag[j])).solve(T(P.M[4 * N + j])) : T(0);
+    d[4] = ip.sa ? SaDiag<T>(odt + T(r3.x)).solve(T(r2.x)) : T(0);
 }
 
 // Coefficients of one cell-face entry's term in the sweeps; face: with the
@@ -1853,10 +1851,11 @@ __global__ __launch_bounds__(256) void k_explicit(Params<T> P)
             double w[5], d[5];
 #pragma unroll
             for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
-            const double kc = P.is[inst].cfl / P.lamc[c];
-#pragma unroll
-            for (int k = 0; k < 4; k++) d[k] = kc * P.M[k * N + c];
-            d[4] = P.ip[inst].sa ? kc * P.M[4 * N + c] : 0.0;
+            const double2 *rec = reinterpret_cast<const double2 *>(P.crec + CR_STRIDE * (size_t)c);
+            const double2 r0 = rec[0], r1 = rec[1], r2 = rec[2], r3 = rec[3];
+            const double kc = P.is[inst].cfl / r3.y;
+            d[0] = kc * r0.x; d[1] = kc * r0.y; d[2] = kc * r1.x; d[3] = kc * r1.y;
+            d[4] = P.ip[inst].sa ? kc * r2.x : 0.0;
             e = apply_update(P, c, inst, P.ip[inst].sa, next_state(P, inst), w, d);
         }
     }
@@ -1898,14 +1897,16 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
     for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
     const int f0 = P.cf_face[MAXV * c + q], j0 = P.cf_nbr[MAXV * c + q], fl0 = P.cf_flag[MAXV * c + q];
-    const int nxt = quad_get<3>(fl0) >> CF_NEXT_SHIFT;
-    const int ovf = nxt ? N + nxt - 1 : -1;   // a polygon's overflow block, or -1
-    const T odt = over_cfl(T(P.lamc[c]), cfl, icfl);
-    const T D = odt + T(P.lsum[c]);
+    // the cell's record, a pair of values on each lane of the quad
+    const double2 rp = reinterpret_cast<const double2 *>(P.crec + CR_STRIDE * (size_t)c)[q];
+    const int ovf = (quad_get<3>(fl0) & CF_POLY) ? P.covf[c] : -1;   // a polygon's overflow block, or -1
+    const T odt = over_cfl(T(quad_get<3>(rp.y)), cfl, icfl);
+    const T D = odt + T(quad_get<2>(rp.y)), sadiag = T(quad_get<3>(rp.x));
     T dws[5], acc[5], t[5];
     if (MODE == SW_FWD || MODE == SW_TOP) {
-#pragma unroll
-        for (int k = 0; k < 5; k++) acc[k] = T(P.M[k * N + c]);
+        acc[0] = T(quad_get<0>(rp.x)); acc[1] = T(quad_get<0>(rp.y));
+        acc[2] = T(quad_get<1>(rp.x)); acc[3] = T(quad_get<1>(rp.y));
+        acc[4] = T(quad_get<2>(rp.x));
         auto lower = [&](int f, int e, int j, int fl) {
 #pragma unroll
             for (int m = 0; m < 5; m++) t[m] = T(0);
@@ -1925,7 +1926,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
             for (int k = 0; k < 4; k++) dws[k] = acc[k] * iD;
         }
-        dws[4] = ip.sa ? SaDiag<T>(odt + T(P.sadiag[c])).solve(acc[4]) : T(0);
+        dws[4] = ip.sa ? SaDiag<T>(odt + sadiag).solve(acc[4]) : T(0);
         if (MODE == SW_FWD) {
             if (q == 0) {
 #pragma unroll
@@ -1964,7 +1965,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
         for (int k = 0; k < 4; k++) d[k] = dws[k] - acc[k] * iD;
     }
-    d[4] = ip.sa ? acc_add(dws[4], SaDiag<T>(odt + T(P.sadiag[c])).solve(acc[4])) : T(0);
+    d[4] = ip.sa ? acc_add(dws[4], SaDiag<T>(odt + sadiag).solve(acc[4])) : T(0);
 #pragma unroll
     for (int k = 0; k < 5; k++) P.dW[k * N + c] = d[k];
     double dd[5];
@@ -2038,7 +2039,7 @@ __global__ __launch_bounds__(256) void k_sweep(Params<T> P, int c0, int c1, int 
 // earlier chunks run on the other waves, a wave loads what its next chunk
 // needs (the entries one turn earlier still) and forms the terms'
 // coefficients.  The increments themselves pass through LDS, a ring of slots
-// in sweep order (cslot); the chunk is run once the chunks of all earlier
+// in sweep order; the chunk is run once the chunks of all earlier
 // wavefronts are counted complete, and adds itself to the count.  What is
 // left in the chain is one LDS read, the product with the increments, the
 // sum over the quad and one LDS write.
@@ -2049,15 +2050,23 @@ __global__ __launch_bounds__(256) void k_sweep(Params<T> P, int c0, int c1, int 
 // bounded all the same, and a wave that ran out of polls marks the
 // instance's update as bad.
 //
-// Measured (forward + backward sweep with its update, us), against a wave per
+// Measured (forward + backward sweep with the update, us), against a wave per
 // block that loaded everything in its turn: 64x32 plate in blocks of 128,
-// 92 -> 38; turbulent plate (100 wavefronts a block) 388 -> 103; 41k aerofoil
-// in blocks of 256, FP32, 119 -> 47; 250k aerofoil, two passes, 745 -> 254;
+// 92 -> 36; turbulent plate (100 wavefronts a block) 388 -> 105; 41k aerofoil
+// in blocks of 256, FP32, 119 -> 42; 250k aerofoil, two passes, 745 -> 186;
 // against one workgroup with a barrier after each wavefront: the polygon
-// cavity in its own order (385 wavefronts) 1940 -> 495.  About 0.37 us a
-// forward wavefront of one chunk, of which the chain's instructions (95
-// FP64 and lane moves at 4 or more cycles) are half and its two LDS trips
-// most of the rest.
+// cavity in its own order (385 wavefronts) 1940 -> 467.  Where wavefronts are
+// single chunks the chain bounds it, 0.4 us a forward wavefront: its
+// instructions (95 FP64 and lane moves at 4 or more cycles) are half and its
+// two LDS trips most of the rest.  Where several groups share a CU or
+// wavefronts have several chunks the CU's memory pipe does (its data unit was
+// 90 % busy on the polygon cavity, at about 20 cache lines an instruction), so
+// a cell's residual and diagonal are one 64-byte record that the quad reads
+// with one instruction, the forward sweep leaves the backward one a record of
+// its own (increment, reciprocal diagonals), slots ride in the entries' flags
+// and chunk table, and entries without a term load the cell's own lines
+// (250k aerofoil 246 -> 186 us, 983k cells in colour order, forward 59 -> 48
+// us; the gather, which writes the records, 97 -> 102 us).
 //
 // The terms and their order are those of sweep_quad, so the iterates are
 // bitwise those of the launch-per-wavefront schedule.  The last backward sweep
@@ -2083,8 +2092,7 @@ __device__ __forceinline__ void put(V *base, unsigned off, V v)
     *reinterpret_cast<V *>(reinterpret_cast<char *>(base) + off) = v;
 }
 
-// A chunk's cells [x, y) and the chunks that must be complete before it in
-// the forward (z) and the backward sweep (w); y <= x past the group's end.
+// A chunk's place (SweepGroups::chunk); no cells past the group's end.
 // Through a vector load: scalar loads share their counter with the LDS
 // accesses of the chain.  (Here and below nothing is loaded under a branch:
 // a lane without a cell or an entry loads from a place that exists, since the
@@ -2096,12 +2104,12 @@ __device__ __forceinline__ int4 chunk_place(const int4 *chunk, int i, int n)
     if (!FWD) k = n - 1 - k;
     asm volatile("" : "+v"(k));
     int4 m = chunk[k];
-    if (i >= n) m.y = -1;
+    if (i >= n) m.y = 0;
     return m;
 }
 // a lane's cell and entry: the chunk's first cell, the lane's place after it
 struct ChunkIdx {
-    int need, c0, f, j, fl;
+    int need, c0, slot0, f, j, fl;
     int dc;     // cell - c0
     bool act;   // the lane has a cell
 };
@@ -2111,25 +2119,25 @@ template <typename T, int KIND, bool ROE>
 struct ChunkRaw {
     static constexpr bool FWD = grp_fwd(KIND);
     static constexpr bool OWN = ROE || KIND == GRP_BWD_UPDATE;   // the cell's own state is needed
-    using Rhs = std::conditional_t<FWD, double, T>;   // M, or the forward sweep's increment
-    int src, bc, slot_c, slot_j, ovf;   // src: SRC_*
-    double w[5], nx, ny, S, lam, sak, lamc, lsum, sadiag;
-    Rhs rhs[5];
+    using Rec = std::conditional_t<FWD, double, T>;
+    int src, bc, slot_j;   // src: SRC_*
+    bool poly;             // the quad's cell has entries beyond the fourth
+    double w[5], nx, ny, S, lam, sak;
+    Rec rx, ry;            // pair q of the cell's record: crec, or the forward sweep's srec
     T dx[KIND == GRP_FWD2 ? 5 : 1];   // a first block pass's increment of the neighbour
     double wc[OWN ? 5 : 1];
-    T di[ROE ? 4 : 1];                // row q of the cell's inverted diagonal block
+    T di[ROE ? 4 : 1];     // row q of the cell's inverted diagonal block
 };
 // what the chunks of a group share
 template <typename T>
 struct GroupRun {
     const double *W;
     double *Wn;        // the state the update writes
-    const int *cslot;
     const int4 *chunk;
     T *dw;             // the ring
     unsigned *done;    // finished chunks
     T cfl, icfl;
-    int n, q, cell, nw, inst;
+    int n, q, cell, nw, inst, slots;
 };
 
 template <typename T, bool FWD>
@@ -2137,7 +2145,9 @@ __device__ __forceinline__ ChunkIdx chunk_entries(const Params<T> &P, const Grou
 {
     ChunkIdx I;
     I.c0 = __builtin_amdgcn_readfirstlane(m.x);
-    I.act = m.x + G.cell < m.y;
+    const int y = __builtin_amdgcn_readfirstlane(m.y);
+    I.act = G.cell < (y & ((1 << CH_SLOT_SHIFT) - 1));
+    I.slot0 = (y >> CH_SLOT_SHIFT) - 1;
     I.need = __builtin_amdgcn_readfirstlane(FWD ? m.z : m.w);
     I.dc = min(G.cell, P.nc - 1 - I.c0);
     const unsigned e = 4u * (unsigned)(MAXV * I.dc + G.q);
@@ -2179,8 +2189,12 @@ __device__ __forceinline__ void entry_gather(const Params<T> &P, const GroupRun<
     R.nx = at(P.enx + e0, oe); R.ny = at(P.eny + e0, oe); R.S = at(P.es + e0, oe);
     R.lam = at(P.flam, of);
     R.sak = at(P.fsak, of);
-    R.bc = grp_fwd(KIND) ? 0 : at(P.fbc, of / 2);
-    R.slot_j = RING ? at(G.cslot, oj / 2) : jw;
+    R.bc = 0;
+    if constexpr (!grp_fwd(KIND)) {
+        const int fb = R.src == SRC_GHOST ? f : __builtin_amdgcn_readfirstlane(f);
+        R.bc = at(P.fbc, 4u * (unsigned)fb);
+    }
+    R.slot_j = RING ? (R.src == SRC_NEAR ? fl >> CF_SLOT_SHIFT : 0) : jw;
     if constexpr (KIND == GRP_FWD2) {
 #pragma unroll
         for (int k = 0; k < 5; k++) R.dx[k] = at(P.dWx + k * N, (unsigned)sizeof(T) * (unsigned)jw);
@@ -2195,15 +2209,16 @@ __device__ __forceinline__ void chunk_gather(const Params<T> &P, const GroupRun<
     entry_gather<T, KIND, RING, ROE>(P, G, I.c0 + I.dc, (size_t)MAXV * I.c0, (unsigned)(MAXV * I.dc + q), I.f, I.j,
                                      I.fl, R);
     if (!I.act) R.src = SRC_NONE;
-    const int nxt = quad_get<3>(I.fl) >> CF_NEXT_SHIFT;
-    R.ovf = I.act && nxt ? P.nc + nxt - 1 : -1;   // a polygon's overflow block, or -1
-    const unsigned o = 8u * (unsigned)I.dc, ot = (unsigned)sizeof(T) * (unsigned)I.dc;
-    R.slot_c = at(G.cslot + I.c0, o / 2);
-    R.lamc = at(P.lamc + I.c0, o); R.lsum = at(P.lsum + I.c0, o); R.sadiag = at(P.sadiag + I.c0, o);
-#pragma unroll
-    for (int k = 0; k < 5; k++) {
-        if constexpr (grp_fwd(KIND)) R.rhs[k] = at(P.M + k * N + I.c0, o);
-        else R.rhs[k] = at(P.dW + k * N + I.c0, ot);
+    R.poly = I.act && (quad_get<3>(I.fl) & CF_POLY);
+    const unsigned o = 8u * (unsigned)I.dc, p = (unsigned)(CR_STRIDE * I.dc + 2 * q);
+    const size_t r0 = (size_t)CR_STRIDE * I.c0;
+    if constexpr (grp_fwd(KIND)) {
+        const double2 v = at(reinterpret_cast<const double2 *>(P.crec + r0), 8u * p);
+        R.rx = v.x; R.ry = v.y;
+    } else {
+        using T2 = std::conditional_t<std::is_same_v<T, double>, double2, float2>;
+        const T2 v = at(reinterpret_cast<const T2 *>(P.srec + r0), (unsigned)sizeof(T) * p);
+        R.rx = v.x; R.ry = v.y;
     }
     if constexpr (ChunkRaw<T, KIND, ROE>::OWN) {
 #pragma unroll
@@ -2296,22 +2311,30 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
     const int q = G.q;
     const bool sa = ip.sa;
     const int c0 = I.c0, dc = I.dc, need = I.need;
-    const bool store = q == 0 && I.act;
+    const bool act = I.act, store = q == 0 && act;
+    int slot_c = I.slot0 + G.cell;
+    slot_c -= slot_c >= G.slots ? G.slots : 0;
     chunk_gather<T, KIND, RING, ROE>(P, G, In, Rn);
     I = chunk_entries<T, FWD>(P, G, place);
     place = chunk_place<FWD>(G.chunk, i + 3 * G.nw, G.n);
     TermCoef<T, ROE> C = entry_coef<T, KIND, ROE>(P, ip, A);
     no_term(C, A.src == SRC_NONE);
     pin_coef(C);
-    T rhs[5];
-#pragma unroll
-    for (int k = 0; k < 5; k++) {
-        rhs[k] = T(A.rhs[k]);
-        pin(rhs[k]);
+    T rhs[5] = {T(quad_get<0>(A.rx)), T(quad_get<0>(A.ry)), T(quad_get<1>(A.rx)), T(quad_get<1>(A.ry)),
+                T(quad_get<2>(A.rx))};
+    T iD, sd;   // 1 / D and what divides the SA component, from the cell's record or as the forward sweep left them
+    if constexpr (FWD) {
+        const T odt = over_cfl(T(quad_get<3>(A.ry)), G.cfl, G.icfl);
+        iD = inv(odt + T(quad_get<2>(A.ry)));
+        sd = sa ? SaDiag<T>(odt + T(quad_get<3>(A.rx))).v : T(1);
+    } else {
+        iD = quad_get<2>(A.ry);
+        sd = quad_get<3>(A.rx);
     }
-    const T odt = over_cfl(T(A.lamc), G.cfl, G.icfl);
-    T iD = inv(odt + T(A.lsum));
-    SaDiag<T> Ds(sa ? odt + T(A.sadiag) : T(1));
+    SaDiag<T> Ds;
+    Ds.v = sd;
+#pragma unroll
+    for (int k = 0; k < 5; k++) pin(rhs[k]);
     pin(iD);
     pin(Ds.v);
     T vw = T(0), vwB = T(0);
@@ -2321,16 +2344,16 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
     // Roe matrices take the registers
     ChunkRaw<T, KIND, ROE> B;
     TermCoef<T, ROE> CB;
-    const bool poly = __any(A.ovf >= 0);
+    const bool poly = __any(A.poly);
     auto overflow = [&]() {
-        const int c = c0 + dc, b = A.ovf >= 0 ? A.ovf : c;
+        const int c = c0 + dc, b = A.poly ? P.covf[c] : c;
         const size_t e = (size_t)MAXV * b + q;
         if constexpr (ROE) {
 #pragma unroll
             for (int k = 0; k < 5; k++) B.wc[k] = A.wc[k];
         }
         entry_gather<T, KIND, RING, ROE>(P, G, c, e, 0u, P.cf_face[e], P.cf_nbr[e], P.cf_flag[e], B);
-        if (A.ovf < 0) B.src = SRC_NONE;
+        if (!A.poly) B.src = SRC_NONE;
         CB = entry_coef<T, KIND, ROE>(P, ip, B);
         no_term(CB, B.src == SRC_NONE);
         pin_coef(CB);
@@ -2402,7 +2425,7 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
     if (store) {
 #pragma unroll
         for (int k = 0; k < 5; k++) {
-            if (RING) G.dw[5 * A.slot_c + k] = d[k];
+            if (RING) G.dw[5 * slot_c + k] = d[k];
             else put(P.dW + k * N + c0, ot, d[k]);
         }
     }
@@ -2422,6 +2445,15 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
             for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
             e40 = apply_update(P, c0 + dc, G.inst, sa, G.Wn, A.wc, dd);
         }
+    } else if constexpr (FWD) {
+        // for the backward sweep: a pair of values from each lane of the quad
+        using T2 = std::conditional_t<std::is_same_v<T, double>, double2, float2>;
+        T2 v;
+        v.x = q < 2 ? (q == 0 ? d[0] : d[2]) : (q == 2 ? d[4] : Ds.v);
+        v.y = q < 2 ? (q == 0 ? d[1] : d[3]) : iD;
+        if (act)
+            put(reinterpret_cast<T2 *>(P.srec + (size_t)CR_STRIDE * c0),
+                (unsigned)sizeof(T) * (unsigned)(CR_STRIDE * dc + 2 * q), v);
     } else if (RING && store) {
 #pragma unroll
         for (int k = 0; k < 5; k++) put(P.dW + k * N + c0, ot, d[k]);
@@ -2448,14 +2480,14 @@ __device__ __forceinline__ double group_sweep(const Params<T> &P, const InstPara
     return e;
 }
 
-// cslot: LDS slot of each cell, negative in a group whose couplings span more
-// cells than the ring holds: its increments pass through global memory
-// instead (all_ring: no such group).  chunk[ch_off[g] .. ch_off[g + 1]): the
-// group's chunks in forward order.  Dynamic LDS: the ring of `slots`
-// increments, then the count of finished chunks.
+// chunk[ch_off[g] .. ch_off[g + 1]): the group's chunks in forward order.  A
+// group whose couplings span more cells than the ring holds (slot -1) passes
+// its increments through global memory instead (all_ring: no such group).
+// Dynamic LDS: the ring of `slots` increments, then the count of finished
+// chunks.
 template <typename T, int KIND, bool ONE, bool ROE>
-__global__ __launch_bounds__(512) void k_sweep_grp(Params<T> P, const int *cslot, const int *ch_off,
-                                                   const int4 *chunk, int slots, int all_ring)
+__global__ __launch_bounds__(64 * (ROE ? GRP_WAVES_ROE : GRP_WAVES)) void k_sweep_grp(
+    Params<T> P, const int *ch_off, const int4 *chunk, int slots, int all_ring)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     GroupRun<T> G;
@@ -2465,7 +2497,7 @@ __global__ __launch_bounds__(512) void k_sweep_grp(Params<T> P, const int *cslot
     G.n = ch_off[blockIdx.x + 1] - k0;
     if (G.n <= 0) return;
     G.chunk = chunk + k0;
-    G.cslot = cslot;
+    G.slots = slots;
     // a group's cells belong to one instance
     G.inst = ONE ? 0 : __builtin_amdgcn_readfirstlane(cell_inst(P, G.chunk[0].x));
     if (!ONE && P.is[G.inst].halt) return;   // the whole workgroup
@@ -2483,7 +2515,7 @@ __global__ __launch_bounds__(512) void k_sweep_grp(Params<T> P, const int *cslot
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     double e;
-    if (all_ring || __builtin_amdgcn_readfirstlane(cslot[G.chunk[0].x]) >= 0)
+    if (all_ring || (G.chunk[0].y >> CH_SLOT_SHIFT) != 0)
         e = group_sweep<T, KIND, true, ROE>(P, ip, G, wave);
     else
         e = group_sweep<T, KIND, false, ROE>(P, ip, G, wave);
@@ -2530,17 +2562,19 @@ __global__ void k_fill_instance(int n, const int *cells, int nc, double w0, doub
     W[c] = w0; W[nc + c] = w1; W[2 * nc + c] = w2; W[3 * nc + c] = w3; W[4 * nc + c] = w4;
 }
 
-// to_instance: dst (5 x nc, internal order) <- src (5 x n, upload order);
-// else the reverse
-__global__ void k_copy_instance(int n, const int *cells, int nc, const double *src, double *dst, int to_instance)
+// to_instance: dst (internal order, component k of cell c at k sk + c sc) <-
+// src (5 x n, upload order); else the reverse
+__global__ void k_copy_instance(int n, const int *cells, size_t sk, size_t sc, const double *src, double *dst,
+                                int to_instance)
 {
     int u = blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= n) return;
     int c = cells[u];
 #pragma unroll
     for (int k = 0; k < 5; k++) {
-        if (to_instance) dst[(size_t)k * nc + c] = src[(size_t)k * n + u];
-        else dst[(size_t)k * n + u] = src[(size_t)k * nc + c];
+        const size_t i = k * sk + c * sc;
+        if (to_instance) dst[i] = src[(size_t)k * n + u];
+        else dst[(size_t)k * n + u] = src[i];
     }
 }
 
@@ -2602,7 +2636,8 @@ static void launch_grp(const Launch &L, const Params<T> &P, const SweepGroups &G
     const bool one = P.ninst == 1, roe = P.dinv != nullptr;
     auto *k = one ? (roe ? k_sweep_grp<T, KIND, true, true> : k_sweep_grp<T, KIND, true, false>)
                   : (roe ? k_sweep_grp<T, KIND, false, true> : k_sweep_grp<T, KIND, false, false>);
-    hipLaunchKernelGGL(k, dim3(G.n), dim3(64 * G.waves), grp_lds(G.slots, sizeof(T)), L.s, P, G.cslot, G.ch_off,
+    const int waves = min(G.waves, roe ? GRP_WAVES_ROE : GRP_WAVES);
+    hipLaunchKernelGGL(k, dim3(G.n), dim3(64 * waves), grp_lds(G.slots, sizeof(T)), L.s, P, G.ch_off,
                        G.chunk, G.slots, G.all_ring ? 1 : 0);
 }
 
@@ -2643,11 +2678,11 @@ void launch_fill_instance(const Launch &L, int n, const int *cells, int nc, cons
     hipLaunchKernelGGL(k_fill_instance, dim3(nblk(n, 256)), dim3(256), 0, L.s, n, cells, nc, Winf[0], Winf[1],
                        Winf[2], Winf[3], Winf[4], W);
 }
-void launch_copy_instance(const Launch &L, int n, const int *cells, int nc, const double *src, double *dst,
+void launch_copy_instance(const Launch &L, int n, const int *cells, size_t sk, size_t sc, const double *src, double *dst,
                           bool to_instance)
 {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_copy_instance, dim3(nblk(n, 256)), dim3(256), 0, L.s, n, cells, nc, src, dst,
+    hipLaunchKernelGGL(k_copy_instance, dim3(nblk(n, 256)), dim3(256), 0, L.s, n, cells, sk, sc, src, dst,
                        to_instance ? 1 : 0);
 }
 
