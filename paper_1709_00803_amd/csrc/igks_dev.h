@@ -79,6 +79,7 @@ struct Params {
     const int *cinst, *finst;  // instance of each cell / face
     const InstParam *ip;
     InstScalars *is;
+    int pend;                  // 1: the iteration before has not been committed (prep, flux, gather, reduce)
     unsigned long long *slot;  // ninst x NSL x NSLOT slots, SLOT_STRIDE apart
     // cell arrays (SoA, internal order)
     double *Wa, *Wb;           // state ping-pong, 5 x nc
@@ -137,7 +138,7 @@ struct Params {
     // cell and its neighbours (which lie in other wavefronts) are read by the
     // same XCD close together in time
     const int *cperm;
-    double *ipart;             // ninst x rb x 2 partial sums
+    double *ipart;             // 2 (of odd and even iterations) x ninst x rb x 2 partial sums
     int rb;                    // partial sums per instance: slices of NORM_SLICE squares
     double *hist;              // HIST_W x ninst x hist_cap
     int hist_cap;
@@ -153,7 +154,8 @@ template <typename T> void launch_reset(const Launch &L, const Params<T> &P, int
 template <typename T> void launch_prep(const Launch &L, const Params<T> &P);
 template <typename T> void launch_flux(const Launch &L, const Params<T> &P);
 template <typename T> void launch_gather(const Launch &L, const Params<T> &P);
-// it: the iteration's index in the current chunk (its history entry)
+// it: the iteration's index in the current chunk (its history entry); with
+// P.pend it also commits iteration it - 1
 template <typename T> void launch_reduce(const Launch &L, const Params<T> &P, int it);
 template <typename T> void launch_roe_diag(const Launch &L, const Params<T> &P);
 // one wavefront of cells [c0, c1) of the sweeps; mode 0 forward, 1 backward,

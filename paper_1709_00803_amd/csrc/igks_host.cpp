@@ -753,7 +753,7 @@ WsMap layout(const Global &G, int ninst, const igks_options &o, int hist_cap)
     w.frr = L.add(2 * F * D); w.fidl = L.add(F * D); w.fidr = L.add(F * D); w.firn = L.add(F * D);
     w.frec = L.add(FR_STRIDE * F * D); w.flam = L.add(F * D); w.fsak = L.add(F * D);
     w.enx = L.add(E * D); w.eny = L.add(E * D); w.es = L.add(E * D);
-    w.ipart = L.add(2 * NI * (size_t)norm_rb(G) * D);
+    w.ipart = L.add(2 * 2 * NI * (size_t)norm_rb(G) * D);
     w.ipos = L.add(N * I);
     w.cperm = L.add(N * I);
     w.hist = L.add((size_t)HIST_W * NI * hist_cap * D);
@@ -829,28 +829,35 @@ SweepGroups groups_of(igks_ctx *c)
     return S;
 }
 
-// queue one nonlinear iteration of every instance
+// Queue iteration `it` of a chunk of n, of every instance.  The commit of an
+// iteration is left to the reduction of the next one and launched by itself
+// only after the last; where the limiter may freeze, the next iteration's
+// preparation needs what the commit finds, and every iteration launches it.
 template <typename T>
-void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it)
+void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it, int n)
 {
+    const bool defer = !(c->opt.limiter && c->opt.limiter_freeze > 0.0);
+    Params<T> Pr = P;
+    Pr.pend = defer && it > 0;
+    const bool commit = !defer || it == n - 1;
     Launch L = launch_of(c);
     const Global &G = c->g;
     const int lev1 = G.nlev > 1 ? G.lev_off[1] : 0;   // cells of the first wavefront
     auto mark = [&](int k) { if (ev) (void)hipEventRecord(ev[k], c->stream); };
     mark(0);
-    launch_prep(L, P);
+    launch_prep(L, Pr);
     mark(1);
-    launch_flux(L, P);
+    launch_flux(L, Pr);
     mark(2);
-    launch_gather(L, P);
+    launch_gather(L, Pr);
     mark(3);
-    launch_reduce(L, P, it);
+    launch_reduce(L, Pr, it);
     mark(4);
     if (c->opt.scheme == 1) {
         // explicit scheme: one update kernel in place of the sweeps
         launch_explicit(L, P);
         mark(5);
-        launch_commit(L, P, it);
+        if (commit) launch_commit(L, P, it);
         mark(6);
         return;
     }
@@ -883,7 +890,7 @@ void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it)
     else
         for (int l = G.nlev - 2; l >= 0; l--) launch_sweep(L, P, G.lev_off[l], G.lev_off[l + 1], 1, lev1);
     mark(6);   // the backward sweeps' class ends here; the commit belongs to no class
-    launch_commit(L, P, it);
+    if (commit) launch_commit(L, P, it);
 }
 
 template <typename T>
@@ -912,7 +919,7 @@ int run_chunk(igks_ctx *c, const Params<T> &P, int k)
         hipEvent_t ev[NKT + 1];
         for (auto &e : ev) HIPCHK(c, hipEventCreate(&e));
         for (int i = 0; i < k; i++) {
-            queue_iteration(c, P, ev, i);
+            queue_iteration(c, P, ev, i, k);
             HIPCHK(c, hipEventSynchronize(ev[NKT]));
             for (int j = 0; j < NKT; j++) {
                 float ms = 0;
@@ -926,7 +933,7 @@ int run_chunk(igks_ctx *c, const Params<T> &P, int k)
         if (!c->gexec) {
             hipGraph_t g;
             HIPCHK(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-            for (int i = 0; i < k; i++) queue_iteration(c, P, nullptr, i);
+            for (int i = 0; i < k; i++) queue_iteration(c, P, nullptr, i, k);
             HIPCHK(c, hipStreamEndCapture(c->stream, &g));
             hipError_t e = hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0);
             (void)hipGraphDestroy(g);
@@ -938,7 +945,7 @@ int run_chunk(igks_ctx *c, const Params<T> &P, int k)
         }
         HIPCHK(c, hipGraphLaunch(c->gexec, c->stream));
     } else {
-        for (int i = 0; i < k; i++) queue_iteration(c, P, nullptr, i);
+        for (int i = 0; i < k; i++) queue_iteration(c, P, nullptr, i, k);
     }
     HIPCHK(c, hipGetLastError());
     const size_t ni = c->inst.size();

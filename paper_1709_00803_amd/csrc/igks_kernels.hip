@@ -373,7 +373,8 @@ __device__ __forceinline__ int live_inst(const Params<T> &P, const int *idx, int
 {
     if (ONE) return 0;
     const int inst = P.ninst == 1 ? 0 : idx[i];
-    return P.is[inst].halt ? -1 : inst;
+    const InstScalars &s = P.is[inst];
+    return (s.halt | (P.pend & s.bad)) ? -1 : inst;
 }
 template <typename T>
 __device__ __forceinline__ int face_inst(const Params<T> &P, int f)
@@ -381,10 +382,13 @@ __device__ __forceinline__ int face_inst(const Params<T> &P, int f)
     return P.ninst == 1 ? 0 : P.finst[f];
 }
 
+// The current state: the buffer ncommit points to, or, while the commit of
+// the iteration before is pending (P.pend), the one it will point to.
 template <typename T>
 __device__ __forceinline__ const double *cur_state(const Params<T> &P, int inst)
 {
-    return (P.is[inst].ncommit & 1) ? P.Wb : P.Wa;
+    const InstScalars &s = P.is[inst];
+    return ((s.ncommit ^ (P.pend & ~s.bad)) & 1) ? P.Wb : P.Wa;
 }
 
 // the other state buffer, which the update writes
@@ -1385,12 +1389,13 @@ __device__ __forceinline__ double wave_sum(double v)
 // slices past the instance's end are empty) of instance i's squares
 // (contiguous, instance-grouped) in a fixed order, so the L2 norms are
 // deterministic without float atomics and the same whatever the other
-// instances of the context; k_commit adds the rb partial sums.
+// instances of the context; the commit adds the rb partial sums.
 template <typename T>
-__device__ __forceinline__ void norm_partial(const Params<T> &P, int blk)
+__device__ __forceinline__ void norm_partial(const Params<T> &P, int blk, int it)
 {
     __shared__ double a[256], b[256];
     int i = blk / P.rb, part = blk % P.rb;
+    double *out = P.ipart + 2 * ((size_t)(it & 1) * P.ninst * P.rb + blk);
     int lo = P.ioff[i], n = P.ioff[i + 1] - lo;
     int s0 = lo + min(n, part * NORM_SLICE), s1 = lo + min(n, (part + 1) * NORM_SLICE);
     double x = 0.0, y = 0.0;
@@ -1408,32 +1413,95 @@ __device__ __forceinline__ void norm_partial(const Params<T> &P, int blk)
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        P.ipart[2 * blk] = a[0];
-        P.ipart[2 * blk + 1] = b[0];
+        out[0] = a[0];
+        out[1] = b[0];
     }
+}
+
+// The commit of iteration `it` of the chunk for instance i, by one wave: the
+// L2 norms from the partial sums (in a fixed order), the drop reference and
+// limiter freezing, then accept (flip the state buffer) or reject and freeze
+// the instance, the Eq.40 maximum.  Returns false for a frozen instance.
+template <typename T>
+__device__ __forceinline__ bool commit_instance(const Params<T> &P, int it, int i, int lane)
+{
+    InstScalars *s = &P.is[i];
+    double e40 = wave_max(slot_lane(P.slot, i, SL_E40));
+    const double *part = P.ipart + 2 * (size_t)P.rb * ((size_t)(it & 1) * P.ninst + i);
+    double x = 0.0, y = 0.0;
+    // unrolled so that the loads of several slices are in flight together
+    // (the sums keep their order)
+#pragma unroll 8
+    for (int k = lane; k < P.rb; k += warpSize) {
+        x += part[2 * k];
+        y += part[2 * k + 1];
+    }
+    x = wave_sum(x);
+    y = wave_sum(y);
+    const int bad = s->bad;
+    *slot_at(P.slot, i, SL_E40, lane) = 0ull;
+    if (lane == 0) {
+        const double l2 = sqrt(x), sal2 = sqrt(y);
+        // the drop is measured from the largest ||M_rho||_2 so far
+        if (s->ncommit == 0 || l2 > s->res0) s->res0 = l2;
+        // limiter freezing: from the next iteration on, the factors just computed
+        if (P.limiter && P.limiter_freeze > 0.0 && !s->phi_frozen && l2 <= P.limiter_freeze * s->res0) s->phi_frozen = 1;
+        s->res_l2 = l2;
+        s->sa_l2 = sal2;
+        s->e40 = e40;
+        if (it < P.hist_cap) {
+            double *e = P.hist + (size_t)HIST_W * ((size_t)it * P.ninst + i);
+            e[0] = l2; e[4] = e40; e[5] = sal2;
+        }
+        if (bad) s->halt = 1;
+        else s->ncommit += 1;
+    }
+    return !bad;
+}
+template <typename T>
+__global__ __launch_bounds__(64) void k_commit(Params<T> P, int it)
+{
+    if (!P.is[blockIdx.x].halt) commit_instance(P, it, blockIdx.x, threadIdx.x);
 }
 
 // Blocks [0, ninst rb): the norm partial sums.  Block ninst rb + i, first
 // wave: the Eq.23 time step the flux used, the max norm, the Eq.25 CFL law
-// (the L2 norms are not needed before the commit), history entry `it` of
-// the chunk.
+// (the L2 norms are not needed before the commit), history entry `it` of the
+// chunk; second wave: the pending commit of the iteration before (P.pend).
+// A launch costs 3.5
+// us and more whatever it does, so a chunk has one k_commit of its own, at its
+// end: until then k_prep, k_flux and k_gather take the instance's state from
+// its scalars as the commit will leave them (cur_state, live_inst), and the
+// partial sums alternate between two halves.  An iteration of the 64x32 plate
+// in blocks 56.8 -> 54.0 us, of the explicit 100x100 cavity 33.9 -> 31.1 us, of
+// the 41k aerofoil in colour order 55.6 -> 52.8 us (with the commit on the CFL
+// law's wave, one after the other, 55.0, 31.4 and 54.1 us).
 template <typename T>
 __global__ __launch_bounds__(256) void k_reduce(Params<T> P, int it)
 {
     if ((int)blockIdx.x < P.ninst * P.rb) {
-        norm_partial(P, blockIdx.x);
+        norm_partial(P, blockIdx.x, it);
         return;
     }
-    const int i = blockIdx.x - P.ninst * P.rb, lane = threadIdx.x;
-    if (lane >= 64) return;
+    const int i = blockIdx.x - P.ninst * P.rb, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave > 1) return;
     InstScalars *s = &P.is[i];
-    if (s->halt) return;
+    // What the commit next door may be writing (halt, ncommit) is used only
+    // in ways that its writes do not change.
+    const int dead = s->halt | (P.pend & s->bad);
+    const bool first = !P.pend && s->ncommit == 0;
+    if (wave == 1) {
+        if (P.pend && !s->halt) commit_instance(P, it - 1, i, lane);
+        return;
+    }
     double dt = wave_min(slot_lane(P.slot, i, SL_DTMIN));
     double rinf = wave_max(slot_lane(P.slot, i, SL_RESINF));
+    if (dead) return;
+    *slot_at(P.slot, i, SL_DTMIN, lane) = 0x7ff0000000000000ull;
     *slot_at(P.slot, i, SL_RESINF, lane) = 0ull;
     if (lane != 0) return;
     s->dt = dt;
-    if (s->ncommit == 0) {
+    if (first) {
         s->cfl = P.cfl_init;
     } else if (P.cfl_mode == 0) {
         double cf = s->cfl * s->res_inf_prev / rinf;
@@ -1972,47 +2040,6 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 #pragma unroll
     for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
     return apply_update(P, c, inst, ip.sa, next_state(P, inst), w, dd);
-}
-
-// One wave per instance (block i): the L2 norms from the partial sums (in
-// a fixed order), the drop reference and limiter freezing, then accept
-// (flip the state buffer) or reject and freeze the instance, the Eq.40
-// maximum, slots reset for the next iteration.
-template <typename T>
-__global__ __launch_bounds__(64) void k_commit(Params<T> P, int it)
-{
-    const int i = blockIdx.x, lane = threadIdx.x;
-    InstScalars *s = &P.is[i];
-    if (s->halt) return;
-    double e40 = wave_max(slot_lane(P.slot, i, SL_E40));
-    double x = 0.0, y = 0.0;
-    // unrolled so that the loads of several slices are in flight together
-    // (the sums keep their order)
-#pragma unroll 8
-    for (int k = lane; k < P.rb; k += warpSize) {
-        x += P.ipart[2 * (i * P.rb + k)];
-        y += P.ipart[2 * (i * P.rb + k) + 1];
-    }
-    x = wave_sum(x);
-    y = wave_sum(y);
-    int bad = s->bad;
-    *slot_at(P.slot, i, SL_DTMIN, lane) = 0x7ff0000000000000ull;
-    *slot_at(P.slot, i, SL_E40, lane) = 0ull;
-    if (lane != 0) return;
-    const double l2 = sqrt(x), sal2 = sqrt(y);
-    // the drop is measured from the largest ||M_rho||_2 so far
-    if (s->ncommit == 0 || l2 > s->res0) s->res0 = l2;
-    // limiter freezing: from the next iteration on, the factors just computed
-    if (P.limiter && P.limiter_freeze > 0.0 && !s->phi_frozen && l2 <= P.limiter_freeze * s->res0) s->phi_frozen = 1;
-    s->res_l2 = l2;
-    s->sa_l2 = sal2;
-    s->e40 = e40;
-    if (it < P.hist_cap) {
-        double *e = P.hist + (size_t)HIST_W * ((size_t)it * P.ninst + i);
-        e[0] = l2; e[4] = e40; e[5] = sal2;
-    }
-    if (bad) s->halt = 1;
-    else s->ncommit += 1;
 }
 
 // One wavefront of cells [c0, c1), four lanes per cell (sweep_quad)
