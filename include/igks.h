@@ -24,7 +24,11 @@
  *   - Host pointers are read or written during the call only (copied); the
  *     caller keeps ownership.  Device memory comes from the caller: the
  *     library asks for a workspace size and works inside that one buffer,
- *     and never allocates or frees device memory itself.
+ *     and never allocates or frees device memory itself.  A context bound to
+ *     a caller's workspace also holds pinned host memory, at most 9 MiB,
+ *     through which it hands out states, residuals and histories; it is freed
+ *     at the next binding and with the context.  (If it cannot be had, calls
+ *     copy without it.)
  *   - All work is queued on the HIP stream given at creation (or, for a
  *     NULL stream, on a stream the library creates at default priority).
  *     Calls that return host data synchronise that stream.

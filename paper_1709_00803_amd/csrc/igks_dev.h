@@ -184,15 +184,26 @@ constexpr size_t grp_lds(int slots, size_t size) { return 5 * size * (size_t)slo
 // sweep, which also updates every cell
 template <typename T>
 void launch_sweep_grp(const Launch &L, const Params<T> &P, const SweepGroups &G, bool fwd, bool update);
-template <typename T> void launch_commit(const Launch &L, const Params<T> &P, int it);
+// mail: null, or host memory (mapped) for the scalars of all instances and
+// then nh history entries, laid out as on the device
+template <typename T> void launch_commit(const Launch &L, const Params<T> &P, int it, double *mail, int nh);
 // explicit step (Eq.15, local time steps) in place of the sweeps
 template <typename T> void launch_explicit(const Launch &L, const Params<T> &P);
 void launch_wall_distance(const Launch &L, int nc, const double *xc, const double *yc, const int *cinst,
                           const int *woff, const double *wseg, double *dwall);
-void launch_gather_faces(const Launch &L, int n, const int *faces, const double *frec, int nf, double *out);
+// beside a copy kernel's copy: the per-iteration slots of instances [lo, hi)
+// back to their neutral values (slot null: nothing); is, if not null, = s
+struct SlotReset {
+    unsigned long long *slot;
+    int lo, hi;
+    InstScalars *is;
+    InstScalars s;
+};
+void launch_gather_faces(const Launch &L, int n, const int *faces, const double *frec, int nf, double *out,
+                         const SlotReset &R);
 void launch_fill_instance(const Launch &L, int n, const int *cells, int nc, const double *Winf, double *W);
 // component k of cell c of the internal array at k sk + c sc
 void launch_copy_instance(const Launch &L, int n, const int *cells, size_t sk, size_t sc, const double *src, double *dst,
-                          bool to_instance);
+                          bool to_instance, const SlotReset &R);
 
 }  // namespace igks

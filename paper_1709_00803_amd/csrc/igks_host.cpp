@@ -7,11 +7,13 @@
 #include "igks_dev.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -73,6 +75,19 @@ struct Buf {
     size_t off, bytes;
 };
 
+// Host staging.  A copy between the device and pageable memory that the
+// runtime stages costs 25 us and more a call, and an array that the caller has
+// just allocated has to be paged in while it is filled, at 13 GB/s from one
+// thread.  So a kernel writes the values into pinned memory, in slots of
+// STAGE_CELLS cells (640 KiB), and the host copies a slot out while the next is
+// written; from STAGE_THREAD_PIECES slots on, STAGE_THREADS threads do.  The
+// state of 2048 cells 58 -> 18 us, of 41k 140 -> 71 us, of 250k (16 pieces) 729 ->
+// 375 us, of 983k (60 pieces) 3980 -> 3260 us with one thread, 2500 with two,
+// 1630 with four and 1390 with eight, which is more than a rank's share of the
+// cores; four slots' worth of cells in one measured the same.
+constexpr int STAGE_CELLS = 16384, STAGE_SLOTS = 8, STAGE_THREADS = 4, STAGE_THREAD_PIECES = 8;
+constexpr size_t STAGE_BYTES = sizeof(double) * 5 * STAGE_CELLS, MAIL_MAX = size_t(4) << 20;
+
 // timed kernel classes: prep, flux, gather, norms, forward sweep, backward sweep with update
 constexpr int NKT = 6;
 
@@ -112,6 +127,15 @@ struct igks_ctx {
     // host copies of the device scalars and the history of the last iterate call
     std::vector<InstScalars> hs;
     std::vector<std::vector<double>> hist;
+    // Pinned host memory between the kernels and the caller's arrays, while a
+    // caller's workspace is bound (null: copies to and from the caller's
+    // pageable arrays): STAGE_SLOTS or fewer slots of STAGE_CELLS cells, then
+    // the mailbox of a chunk's last commit (null if it would exceed MAIL_MAX).
+    char *pin = nullptr;
+    int pin_slots = 0;
+    int dev = -1;                      // the stream's device
+    double *mail = nullptr;
+    hipEvent_t pin_ev[STAGE_SLOTS] = {};
     // graph of one chunk
     hipGraphExec_t gexec = nullptr;
     int gexec_k = 0;                   // iterations captured in gexec
@@ -149,6 +173,58 @@ int fail(igks_ctx *c, int code, const std::string &msg)
         hipError_t e_ = (call);                                                                     \
         if (e_ != hipSuccess) return fail(ctx, IGKS_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
+
+// Pinned memory may be allocated and freed while another thread captures a
+// graph: nothing here is part of its work.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+void free_pinned(igks_ctx *c)
+{
+    RelaxedCapture relaxed;
+    for (auto &e : c->pin_ev) {
+        if (e) (void)hipEventDestroy(e);
+        e = nullptr;
+    }
+    if (c->pin) (void)hipHostFree(c->pin);
+    c->pin = nullptr;
+    c->mail = nullptr;
+    c->pin_slots = 0;
+}
+
+// the context's pinned memory for the bound mesh; without it (an allocation
+// that fails, another device current than the stream's) every call still works
+void alloc_pinned(igks_ctx *c)
+{
+    const size_t ni = c->inst.size();
+    const size_t mail = ni * (sizeof(InstScalars) + sizeof(double) * HIST_W * (size_t)c->hist_cap);
+    const int slots = std::min(STAGE_SLOTS, (c->g.max_inst_cells + STAGE_CELLS - 1) / STAGE_CELLS);
+    RelaxedCapture relaxed;
+    void *p = nullptr;
+    int cur = -1;
+    if (hipGetDevice(&cur) != hipSuccess || hipStreamGetDevice(c->stream, &c->dev) != hipSuccess || cur != c->dev) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (hipHostMalloc(&p, slots * STAGE_BYTES + (mail <= MAIL_MAX ? mail : 0),
+                      hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    c->pin = (char *)p;
+    c->pin_slots = slots;
+    for (int k = 0; k < slots; k++)
+        if (hipEventCreateWithFlags(&c->pin_ev[k], hipEventDisableTiming | hipEventReleaseToSystem) != hipSuccess) {
+            (void)hipGetLastError();
+            c->pin_ev[k] = nullptr;
+            free_pinned(c);
+            return;
+        }
+    if (mail <= MAIL_MAX) c->mail = (double *)(c->pin + slots * STAGE_BYTES);
+}
 
 void destroy_graph(igks_ctx *c)
 {
@@ -840,6 +916,8 @@ void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it, in
     Params<T> Pr = P;
     Pr.pend = defer && it > 0;
     const bool commit = !defer || it == n - 1;
+    double *mail = it == n - 1 ? c->mail : nullptr;
+    const int nh = std::min(n, c->hist_cap);
     Launch L = launch_of(c);
     const Global &G = c->g;
     const int lev1 = G.nlev > 1 ? G.lev_off[1] : 0;   // cells of the first wavefront
@@ -857,7 +935,7 @@ void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it, in
         // explicit scheme: one update kernel in place of the sweeps
         launch_explicit(L, P);
         mark(5);
-        if (commit) launch_commit(L, P, it);
+        if (commit) launch_commit(L, P, it, mail, nh);
         mark(6);
         return;
     }
@@ -890,7 +968,7 @@ void queue_iteration(igks_ctx *c, const Params<T> &P, hipEvent_t *ev, int it, in
     else
         for (int l = G.nlev - 2; l >= 0; l--) launch_sweep(L, P, G.lev_off[l], G.lev_off[l + 1], 1, lev1);
     mark(6);   // the backward sweeps' class ends here; the commit belongs to no class
-    if (commit) launch_commit(L, P, it);
+    if (commit) launch_commit(L, P, it, mail, nh);
 }
 
 template <typename T>
@@ -951,22 +1029,31 @@ int run_chunk(igks_ctx *c, const Params<T> &P, int k)
     const size_t ni = c->inst.size();
     std::vector<int> n0(ni), h0(ni);
     for (size_t i = 0; i < ni; i++) { n0[i] = c->hs[i].ncommit; h0[i] = c->hs[i].halt; }
-    int rc = sync_scalars(c);
-    if (rc) return rc;
     const int nh = std::min(k, c->hist_cap);
-    if (nh > 0) {
-        std::vector<double> h((size_t)HIST_W * ni * nh);
-        HIPCHK(c, hipMemcpyAsync(h.data(), P.hist, sizeof(double) * h.size(), hipMemcpyDeviceToHost, c->stream));
+    std::vector<double> copied;
+    const double *h = c->mail;
+    if (h && k > 0) {
         HIPCHK(c, hipStreamSynchronize(c->stream));
-        c->hist.resize(ni);
-        for (size_t i = 0; i < ni; i++) {
-            // entries of the iterations this instance ran: the committed ones
-            // and the rejected one that froze it
-            int ran = c->hs[i].ncommit - n0[i] + ((c->hs[i].halt && !h0[i]) ? 1 : 0);
-            for (int e = 0; e < std::min(nh, ran); e++) {
-                const double *src = &h[(size_t)HIST_W * ((size_t)e * ni + i)];
-                c->hist[i].insert(c->hist[i].end(), src, src + HIST_W);
-            }
+        std::memcpy(c->hs.data(), h, sizeof(InstScalars) * ni);
+        h += ni * sizeof(InstScalars) / sizeof(double);
+    } else {
+        int rc = sync_scalars(c);
+        if (rc) return rc;
+        copied.resize((size_t)HIST_W * ni * nh);
+        if (nh > 0) {
+            HIPCHK(c, hipMemcpyAsync(copied.data(), P.hist, sizeof(double) * copied.size(), hipMemcpyDeviceToHost, c->stream));
+            HIPCHK(c, hipStreamSynchronize(c->stream));
+        }
+        h = copied.data();
+    }
+    c->hist.resize(ni);
+    for (size_t i = 0; i < ni; i++) {
+        // entries of the iterations this instance ran: the committed ones
+        // and the rejected one that froze it
+        int ran = c->hs[i].ncommit - n0[i] + ((c->hs[i].halt && !h0[i]) ? 1 : 0);
+        for (int e = 0; e < std::min(nh, ran); e++) {
+            const double *src = &h[(size_t)HIST_W * ((size_t)e * ni + i)];
+            c->hist[i].insert(c->hist[i].end(), src, src + HIST_W);
         }
     }
     return IGKS_OK;
@@ -1030,6 +1117,67 @@ const int *inst_cells(igks_ctx *c, int i) { return (const int *)(c->ws + c->w.g2
 double *cur_buffer(igks_ctx *c, int i) { return (c->hs[i].ncommit & 1) ? c->P64.Wb : c->P64.Wa; }
 
 double *stage_buffer(igks_ctx *c) { return (double *)(c->ws + c->w.stage.off); }
+
+SlotReset reset_slots(igks_ctx *c, int lo, int hi) { return SlotReset{c->P64.slot, lo, hi, nullptr, InstScalars{}}; }
+
+// Five values per cell of an instance (component k of internal cell c at
+// src + k sk + c sc) into the caller's dst[k nc + u], u the upload index; R:
+// what the copy kernel does besides.  The values are there on return.
+int copy_out(igks_ctx *c, int inst, size_t sk, size_t sc, const double *src, double *dst, const SlotReset &R)
+{
+    const int n = c->inst[inst].nc;
+    const int *cells = inst_cells(c, inst);
+    const Launch L = launch_of(c);
+    if (!c->pin || !dst) {
+        launch_copy_instance(L, n, cells, sk, sc, src, stage_buffer(c), false, R);
+        HIPCHK(c, hipGetLastError());
+        if (dst) HIPCHK(c, hipMemcpyAsync(dst, stage_buffer(c), sizeof(double) * 5 * n, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        return IGKS_OK;
+    }
+    const int pieces = (n + STAGE_CELLS - 1) / STAGE_CELLS;
+    const int threads = pieces >= STAGE_THREAD_PIECES ? STAGE_THREADS : 1;
+    const int depth = std::min(pieces, c->pin_slots / threads);   // slots of a thread
+    std::atomic<int> err{(int)hipSuccess};
+    // Pieces t, t + threads, ... through the slots of thread t: `depth` of
+    // them are queued ahead of the one that is copied out.
+    auto work = [&](int t) {
+        if (t > 0 && hipSetDevice(c->dev) != hipSuccess) { err = (int)hipErrorInvalidDevice; return; }
+        auto queue = [&](int j) {
+            const int p = t + j * threads, u0 = p * STAGE_CELLS, m = std::min(STAGE_CELLS, n - u0);
+            if (p >= pieces) return;
+            const int slot = t * depth + j % depth;
+            launch_copy_instance(L, m, cells + u0, sk, sc, src, (double *)(c->pin + slot * STAGE_BYTES), false,
+                                 p == 0 ? R : SlotReset{});
+            hipError_t e = hipGetLastError();
+            if (e == hipSuccess) e = hipEventRecord(c->pin_ev[slot], c->stream);
+            if (e != hipSuccess) err = (int)e;
+        };
+        for (int j = 0; j < depth; j++) queue(j);
+        for (int j = 0; t + j * threads < pieces && err == (int)hipSuccess; j++) {
+            const int u0 = (t + j * threads) * STAGE_CELLS, m = std::min(STAGE_CELLS, n - u0), slot = t * depth + j % depth;
+            const hipError_t e = hipEventSynchronize(c->pin_ev[slot]);
+            if (e != hipSuccess) { err = (int)e; return; }
+            const double *v = (const double *)(c->pin + slot * STAGE_BYTES);
+            for (int k = 0; k < 5; k++) std::memcpy(dst + (size_t)k * n + u0, v + (size_t)k * m, sizeof(double) * m);
+            queue(j + depth);
+        }
+    };
+    std::thread th[STAGE_THREADS];
+    int started = 1;
+    try {
+        for (; started < threads; started++) th[started] = std::thread(work, started);
+    } catch (...) {
+        // no more threads: their pieces are done below
+    }
+    work(0);
+    for (int t = 1; t < started; t++) th[t].join();
+    for (int t = started; t < threads; t++) work(t);
+    const hipError_t e = (hipError_t)err.load(), es = hipStreamSynchronize(c->stream);
+    if (e != hipSuccess || es != hipSuccess)
+        return fail(c, IGKS_EHIP, std::string("copy to the host: ") + hipGetErrorString(e != hipSuccess ? e : es));
+    return IGKS_OK;
+}
 
 // FARFIELD faces: free stream where V_inf . n < 0, else Riemann outflow
 int upload_bc(igks_ctx *c)
@@ -1216,6 +1364,7 @@ void igks_destroy(igks_ctx *c)
 {
     if (!c) return;
     destroy_graph(c);
+    free_pinned(c);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -1310,15 +1459,15 @@ int igks_workspace_size(const igks_ctx *cc, size_t *bytes)
     return IGKS_OK;
 }
 
-int igks_bind_workspace(igks_ctx *c, void *dptr, size_t bytes)
+static int bind_workspace(igks_ctx *c, void *dptr, size_t bytes, bool pinned)
 {
-    if (!c) return IGKS_EINVAL;
     int rc = ensure_combined(c);
     if (rc) return rc;
     WsMap w = layout(c->g, (int)c->inst.size(), c->opt, c->hist_cap);
     if (!dptr || bytes < w.total) return fail(c, IGKS_ENOMEM, "workspace smaller than igks_workspace_size");
     if (((uintptr_t)dptr) % 256 != 0) return fail(c, IGKS_EINVAL, "workspace must be 256-byte aligned");
     destroy_graph(c);
+    free_pinned(c);
     c->bound = false;
     c->static_dev = -1;
     c->ws = (char *)dptr;
@@ -1380,9 +1529,15 @@ int igks_bind_workspace(igks_ctx *c, void *dptr, size_t bytes)
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->bound = true;
+    if (pinned) alloc_pinned(c);
     for (auto &m : c->inst) m.have_flow = false;
     for (auto &h : c->hist) h.clear();
     return sync_scalars(c);
+}
+
+int igks_bind_workspace(igks_ctx *c, void *dptr, size_t bytes)
+{
+    return c ? bind_workspace(c, dptr, bytes, true) : IGKS_EINVAL;
 }
 
 int igks_bind_static_workspace(igks_ctx *c)
@@ -1411,7 +1566,7 @@ int igks_bind_static_workspace(igks_ctx *c)
         ptr = static_ws[dev].ptr;
         gen = ++static_ws[dev].gen;
     }
-    rc = igks_bind_workspace(c, ptr, STATIC_WS_BYTES);
+    rc = bind_workspace(c, ptr, STATIC_WS_BYTES, false);   // its callers may not allocate
     if (rc) return rc;
     c->static_dev = dev;
     c->static_gen = gen;
@@ -1519,13 +1674,7 @@ int igks_batch_get_state(igks_ctx *c, int32_t inst, double *W)
     int rc = check_inst_ready(c, inst);
     if (rc) return rc;
     if (!W) return IGKS_EINVAL;
-    const int n = c->inst[inst].nc;
-    Launch L = launch_of(c);
-    launch_copy_instance(L, n, inst_cells(c, inst), c->g.N, 1, cur_buffer(c, inst), stage_buffer(c), false);
-    HIPCHK(c, hipGetLastError());
-    HIPCHK(c, hipMemcpyAsync(W, stage_buffer(c), sizeof(double) * 5 * n, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    return IGKS_OK;
+    return copy_out(c, inst, c->g.N, 1, cur_buffer(c, inst), W, SlotReset{});
 }
 
 int igks_get_state(igks_ctx *c, double *W) { return igks_batch_get_state(c, 0, W); }
@@ -1544,15 +1693,24 @@ int igks_batch_set_state(igks_ctx *c, int32_t inst, const double *W, const igks_
     }
     if (sc && sc->iteration < 0) return fail(c, IGKS_EINVAL, "negative iteration count in the scalars");
     InstScalars s = fresh_scalars(sc);
-    HIPCHK(c, hipMemcpyAsync(c->P64.is + inst, &s, sizeof s, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(stage_buffer(c), W, sizeof(double) * 5 * n, hipMemcpyHostToDevice, c->stream));
-    Launch L = launch_of(c);
-    launch_reset(L, c->P64, 1, inst);
-    launch_copy_instance(L, n, inst_cells(c, inst), c->g.N, 1, stage_buffer(c),
-                         (s.ncommit & 1) ? c->P64.Wb : c->P64.Wa, true);
+    // the copy kernel reads a small state from the pinned memory itself
+    double *from = stage_buffer(c);
+    if (c->pin && n <= STAGE_CELLS) {
+        from = (double *)c->pin;
+        std::memcpy(from, W, sizeof(double) * 5 * n);
+    } else {
+        HIPCHK(c, hipMemcpyAsync(from, W, sizeof(double) * 5 * n, hipMemcpyHostToDevice, c->stream));
+    }
+    SlotReset R = reset_slots(c, inst, inst + 1);
+    R.is = c->P64.is + inst;
+    R.s = s;
+    launch_copy_instance(launch_of(c), n, inst_cells(c, inst), c->g.N, 1, from,
+                         (s.ncommit & 1) ? c->P64.Wb : c->P64.Wa, true, R);
     HIPCHK(c, hipGetLastError());
     c->hist[inst].clear();
-    return sync_scalars(c);
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    c->hs[inst] = s;
+    return IGKS_OK;
 }
 
 int igks_set_state(igks_ctx *c, const double *W, const igks_scalars *sc) { return igks_batch_set_state(c, 0, W, sc); }
@@ -1571,7 +1729,9 @@ int igks_batch_get_scalars(igks_ctx *c, int32_t inst, igks_scalars *out)
 
 int igks_get_scalars(igks_ctx *c, igks_scalars *out) { return igks_batch_get_scalars(c, 0, out); }
 
-// residual evaluation of every live instance without advancing the iteration
+// Residual evaluation of every live instance without advancing the iteration.
+// The slots are neutral before it, as every call leaves them; the copy that
+// follows it resets them again.
 static int eval_residual(igks_ctx *c, int inst)
 {
     // the kernels run over every instance, so every instance needs its flow
@@ -1580,10 +1740,7 @@ static int eval_residual(igks_ctx *c, int inst)
     rc = check_ready(c, true);
     if (rc) return rc;
     if (c->hs[inst].halt) return fail(c, IGKS_ENONPHYS, "instance is frozen after a rejected update");
-    Launch L = launch_of(c);
-    launch_reset(L, c->P64, 1, -1);
     queue_residual(c, c->P64);
-    launch_reset(L, c->P64, 1, -1);
     HIPCHK(c, hipGetLastError());
     return IGKS_OK;
 }
@@ -1592,13 +1749,7 @@ int igks_batch_compute_residual(igks_ctx *c, int32_t inst, double *M)
 {
     int rc = eval_residual(c, inst);
     if (rc) return rc;
-    const int n = c->inst[inst].nc;
-    Launch L = launch_of(c);
-    launch_copy_instance(L, n, inst_cells(c, inst), 1, CR_STRIDE, c->P64.crec, stage_buffer(c), false);
-    HIPCHK(c, hipGetLastError());
-    if (M) HIPCHK(c, hipMemcpyAsync(M, stage_buffer(c), sizeof(double) * 5 * n, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
-    return IGKS_OK;
+    return copy_out(c, inst, 1, CR_STRIDE, c->P64.crec, M, reset_slots(c, 0, (int)c->inst.size()));
 }
 
 int igks_compute_residual(igks_ctx *c, double *M) { return igks_batch_compute_residual(c, 0, M); }
@@ -1608,13 +1759,16 @@ int igks_batch_get_wall_loads(igks_ctx *c, int32_t inst, double *cl, double *cd,
     int rc = eval_residual(c, inst);
     if (rc) return rc;
     const int w0 = c->g.woff[inst], nw = c->g.woff[inst + 1] - w0;
-    double *wout = (double *)(c->ws + c->w.wall_out.off);
-    Launch L = launch_of(c);
-    launch_gather_faces(L, nw, (const int *)(c->ws + c->w.wall_faces.off) + w0, c->P64.frec, c->g.F, wout);
+    const bool pinned = c->pin && sizeof(double) * 4 * nw <= STAGE_BYTES;
+    double *wout = pinned ? (double *)c->pin : (double *)(c->ws + c->w.wall_out.off);
+    launch_gather_faces(launch_of(c), nw, (const int *)(c->ws + c->w.wall_faces.off) + w0, c->P64.frec, c->g.F, wout,
+                        reset_slots(c, 0, (int)c->inst.size()));
     HIPCHK(c, hipGetLastError());
-    std::vector<double> fw(4 * (size_t)std::max(nw, 1));
-    if (nw > 0) HIPCHK(c, hipMemcpyAsync(fw.data(), wout, sizeof(double) * 4 * nw, hipMemcpyDeviceToHost, c->stream));
+    std::vector<double> copied(pinned ? 0 : 4 * (size_t)nw);
+    if (!copied.empty())
+        HIPCHK(c, hipMemcpyAsync(copied.data(), wout, sizeof(double) * copied.size(), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    const double *fw = pinned ? wout : copied.data();
     const InstMesh &m = c->inst[inst];
     const double a = m.alpha * M_PI / 180.0, ca = std::cos(a), sa = std::sin(a), q = 0.5;
     double Fx = 0, Fy = 0;

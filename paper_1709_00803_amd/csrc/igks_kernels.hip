@@ -1458,10 +1458,25 @@ __device__ __forceinline__ bool commit_instance(const Params<T> &P, int it, int 
     }
     return !bad;
 }
+// The last commit of a chunk also leaves the instance's scalars and its nh
+// history entries in the caller's mailbox in host memory (mail; null: the
+// caller copies them), which saves two copies and their waits, about 50 us a
+// chunk.
 template <typename T>
-__global__ __launch_bounds__(64) void k_commit(Params<T> P, int it)
+__global__ __launch_bounds__(64) void k_commit(Params<T> P, int it, double *mail, int nh)
 {
-    if (!P.is[blockIdx.x].halt) commit_instance(P, it, blockIdx.x, threadIdx.x);
+    const int i = blockIdx.x, lane = threadIdx.x;
+    if (!P.is[i].halt) commit_instance(P, it, i, lane);
+    if (!mail) return;
+    __threadfence_block();   // lane 0's stores are read by the other lanes
+    constexpr int SW = sizeof(InstScalars) / sizeof(double);
+    const double *s = reinterpret_cast<const double *>(P.is + i);
+    for (int k = lane; k < SW; k += 64) mail[i * SW + k] = s[k];
+    double *h = mail + SW * P.ninst;
+    for (int k = lane; k < HIST_W * nh; k += 64) {
+        const size_t e = HIST_W * ((size_t)(k / HIST_W) * P.ninst + i) + k % HIST_W;
+        h[e] = P.hist[e];
+    }
 }
 
 // Blocks [0, ninst rb): the norm partial sums.  Block ninst rb + i, first
@@ -2568,9 +2583,22 @@ __global__ __launch_bounds__(256) void k_wall_distance(int nc, const double *xc,
     d[c] = best;
 }
 
-__global__ void k_gather_faces(int n, const int *faces, const double *frec, int nf, double *out)
+// What a copy kernel does beside its copy (SlotReset): the slots of instances
+// [lo, hi) back to their neutral values, and an instance's scalars.
+__device__ __forceinline__ void slot_reset(const SlotReset &R, int t, int nt)
+{
+    if (!R.slot) return;
+    for (int k = t; k < (R.hi - R.lo) * NSL * NSLOT; k += nt) {
+        const int i = R.lo + k / (NSL * NSLOT), w = k / NSLOT % NSL;
+        *slot_at(R.slot, i, w, k % NSLOT) = w == SL_DTMIN ? 0x7ff0000000000000ull : 0ull;
+    }
+    if (t == 0 && R.is) *R.is = R.s;
+}
+
+__global__ void k_gather_faces(int n, const int *faces, const double *frec, int nf, double *out, SlotReset R)
 {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
+    slot_reset(R, i, gridDim.x * blockDim.x);
     if (i >= n) return;
     int f = faces[i];
     const double *r = frec + FR_STRIDE * (size_t)f;
@@ -2592,9 +2620,10 @@ __global__ void k_fill_instance(int n, const int *cells, int nc, double w0, doub
 // to_instance: dst (internal order, component k of cell c at k sk + c sc) <-
 // src (5 x n, upload order); else the reverse
 __global__ void k_copy_instance(int n, const int *cells, size_t sk, size_t sc, const double *src, double *dst,
-                                int to_instance)
+                                int to_instance, SlotReset R)
 {
     int u = blockIdx.x * blockDim.x + threadIdx.x;
+    slot_reset(R, u, gridDim.x * blockDim.x);
     if (u >= n) return;
     int c = cells[u];
 #pragma unroll
@@ -2629,9 +2658,9 @@ template <typename T> void launch_explicit(const Launch &L, const Params<T> &P)
 {
     LAUNCH_ONE(k_explicit, T, dim3(nblk(P.nc, L.block[0])), dim3(L.block[0]), P);
 }
-template <typename T> void launch_commit(const Launch &L, const Params<T> &P, int it)
+template <typename T> void launch_commit(const Launch &L, const Params<T> &P, int it, double *mail, int nh)
 {
-    hipLaunchKernelGGL(k_commit<T>, dim3(P.ninst), dim3(64), 0, L.s, P, it);
+    hipLaunchKernelGGL(k_commit<T>, dim3(P.ninst), dim3(64), 0, L.s, P, it, mail, nh);
 }
 template <typename T> void launch_flux(const Launch &L, const Params<T> &P)
 {
@@ -2694,10 +2723,10 @@ void launch_wall_distance(const Launch &L, int nc, const double *xc, const doubl
 {
     hipLaunchKernelGGL(k_wall_distance, dim3(nblk(nc, 256)), dim3(256), 0, L.s, nc, xc, yc, cinst, woff, wseg, dwall);
 }
-void launch_gather_faces(const Launch &L, int n, const int *faces, const double *frec, int nf, double *out)
+void launch_gather_faces(const Launch &L, int n, const int *faces, const double *frec, int nf, double *out,
+                         const SlotReset &R)
 {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_gather_faces, dim3(nblk(n, 256)), dim3(256), 0, L.s, n, faces, frec, nf, out);
+    hipLaunchKernelGGL(k_gather_faces, dim3(nblk(max(n, 1), 256)), dim3(256), 0, L.s, n, faces, frec, nf, out, R);
 }
 void launch_fill_instance(const Launch &L, int n, const int *cells, int nc, const double *Winf, double *W)
 {
@@ -2706,11 +2735,11 @@ void launch_fill_instance(const Launch &L, int n, const int *cells, int nc, cons
                        Winf[2], Winf[3], Winf[4], W);
 }
 void launch_copy_instance(const Launch &L, int n, const int *cells, size_t sk, size_t sc, const double *src, double *dst,
-                          bool to_instance)
+                          bool to_instance, const SlotReset &R)
 {
     if (n <= 0) return;
     hipLaunchKernelGGL(k_copy_instance, dim3(nblk(n, 256)), dim3(256), 0, L.s, n, cells, sk, sc, src, dst,
-                       to_instance ? 1 : 0);
+                       to_instance ? 1 : 0, R);
 }
 
 #define INST(T)                                                                                    \
@@ -2721,7 +2750,7 @@ void launch_copy_instance(const Launch &L, int n, const int *cells, size_t sk, s
     template void launch_reduce<T>(const Launch &, const Params<T> &, int);                        \
     template void launch_roe_diag<T>(const Launch &, const Params<T> &);                           \
     template void launch_sweep<T>(const Launch &, const Params<T> &, int, int, int, int);          \
-    template void launch_commit<T>(const Launch &, const Params<T> &, int);                        \
+    template void launch_commit<T>(const Launch &, const Params<T> &, int, double *, int);                        \
     template void launch_explicit<T>(const Launch &, const Params<T> &);                           \
     template void launch_sweep_grp<T>(const Launch &, const Params<T> &, const SweepGroups &, bool, bool);
 INST(double)

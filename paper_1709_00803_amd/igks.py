@@ -260,13 +260,14 @@ class Solver(_Context):
         return r.as_dict()
 
     def history(self, max_entries=1 << 20):
-        out = np.zeros((max_entries, HIST_W))
         n = C.c_int32()
-        self._chk(igks_get_history(self.ctx, out.ctypes.data_as(_DP), max_entries, C.byref(n)))
-        return out[:n.value]
+        self._chk(igks_get_history(self.ctx, None, max_entries, C.byref(n)))
+        out = np.empty((n.value, HIST_W))
+        self._chk(igks_get_history(self.ctx, out.ctypes.data_as(_DP), n.value, C.byref(n)))
+        return out
 
     def get_state(self):
-        W = np.zeros((5, self.n))
+        W = np.empty((5, self.n))
         self._chk(igks_get_state(self.ctx, W.ctypes.data_as(_DP)))
         return W
 
@@ -280,7 +281,7 @@ class Solver(_Context):
         return s
 
     def compute_residual(self):
-        M = np.zeros((5, self.n))
+        M = np.empty((5, self.n))
         self._chk(igks_compute_residual(self.ctx, M.ctypes.data_as(_DP)))
         return M
 
@@ -330,13 +331,14 @@ class BatchSolver(_Context):
         return r.as_dict()
 
     def history(self, i, max_entries=1 << 20):
-        out = np.zeros((max_entries, HIST_W))
         n = C.c_int32()
-        self._chk(igks_batch_get_history(self.ctx, i, out.ctypes.data_as(_DP), max_entries, C.byref(n)))
-        return out[:n.value]
+        self._chk(igks_batch_get_history(self.ctx, i, None, max_entries, C.byref(n)))
+        out = np.empty((n.value, HIST_W))
+        self._chk(igks_batch_get_history(self.ctx, i, out.ctypes.data_as(_DP), n.value, C.byref(n)))
+        return out
 
     def get_state(self, i):
-        W = np.zeros((5, self.n[i]))
+        W = np.empty((5, self.n[i]))
         self._chk(igks_batch_get_state(self.ctx, i, W.ctypes.data_as(_DP)))
         return W
 
@@ -350,7 +352,7 @@ class BatchSolver(_Context):
         return s
 
     def compute_residual(self, i):
-        M = np.zeros((5, self.n[i]))
+        M = np.empty((5, self.n[i]))
         self._chk(igks_batch_compute_residual(self.ctx, i, M.ctypes.data_as(_DP)))
         return M
 
