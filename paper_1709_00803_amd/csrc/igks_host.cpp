@@ -567,16 +567,18 @@ void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vecto
         nfronts += rng[b].size();
         G.ch_off[b + 1] = (int)G.chunk.size();
     }
-    // Four waves, one per SIMD, take turns where a wavefront is mostly one
-    // chunk or where the groups fill the CUs; where few groups have wider
-    // wavefronts, twelve (three per SIMD, what the registers hold; eight with
-    // the Roe operator) run their chunks at once.  Forward + backward sweep in
-    // us with 4 / 8 / 12 waves: 64x32 plate, 21 blocks 36 / 36 / 37; 250k
-    // aerofoil, 523 blocks of 1.8 chunks a wavefront, 188 / 216 / 225; in natural
-    // order the plate 130 / 109 / 109, the polygon cavity 697 / 490 / 467, the
-    // 100x100 cavity (3.6 chunks a wavefront) 496 / 332 / 298.
+    // Where the groups fill the CUs, four waves each, one per SIMD, take turns;
+    // fewer groups get eight, so that a wave has time for its loads and its
+    // update between its turns, and where their wavefronts are wider than a
+    // chunk twelve (three per SIMD, what the registers hold; eight with the Roe
+    // operator), which run side by side.  Forward + backward sweep in us with
+    // 4 / 8 / 12 waves: 64x32 plate, 21 blocks 33 / 31 / 31; turbulent plate, 60
+    // blocks 93 / 83 / 83; 250k aerofoil, 523 blocks of 1.8 chunks a wavefront
+    // 178 / 199 / 209; in natural order the plate 125 / 98 / 94, the polygon
+    // cavity 683 / 456 / 398, the 100x100 cavity (3.6 chunks a wavefront) 488 /
+    // 327 / 288.
     const double per_front = (double)G.chunk.size() / std::max<size_t>(1, nfronts);
-    G.grp_waves = per_front > 1.35 && ngb <= 256 ? 12 : 4;
+    G.grp_waves = ngb > 256 ? 4 : per_front > 1.35 ? 12 : 8;
 }
 
 // Concatenate the instances in the internal order: cells by (wavefront,

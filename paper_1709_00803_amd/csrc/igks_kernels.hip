@@ -1567,15 +1567,43 @@ __device__ __forceinline__ double quad_get(double v)
     const int lo = quad_get<K>((int)(b & 0xffffffffll)), hi = quad_get<K>((int)(b >> 32));
     return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
-// a -= t_0, t_1, t_2, t_3 (SUB) or a += them, in lane order, t_k the value
-// on lane k of the quad: the order of the one-lane loop over four entries
-template <bool SUB, typename V>
-__device__ __forceinline__ V quad_fold(V a, V t)
+// The value of the lane's neighbour in its quad, lane ^ 1 (X = 1) or lane ^ 2.
+template <int X>
+__device__ __forceinline__ double quad_xor(double v)
 {
-    const V t0 = quad_get<0>(t), t1 = quad_get<1>(t), t2 = quad_get<2>(t), t3 = quad_get<3>(t);
+    constexpr int PERM = X == 1 ? 0xB1 : 0x4E;
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffll), PERM, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), PERM, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+// a less (SUB) or plus t_0, t_1, t_2, t_3, t_k the value on lane k of the quad.
+// FP32: one after another, in lane order.  FP64: (t_0 + t_1) + (t_2 + t_3) first,
+// the same number on every lane, in 7 instructions instead of 12: the fold of the
+// five components was most of what a chunk's turn in the group sweep
+// issued (turbulent plate, 100 wavefronts a block, forward 44 -> 40 us;
+// polygon cavity, 385 wavefronts, 205 -> 180 us).
+template <bool SUB>
+__device__ __forceinline__ float quad_fold(float a, float t)
+{
+    const float t0 = quad_get<0>(t), t1 = quad_get<1>(t), t2 = quad_get<2>(t), t3 = quad_get<3>(t);
     if (SUB) return acc_sub(acc_sub(acc_sub(acc_sub(a, t0), t1), t2), t3);
     return acc_add(acc_add(acc_add(acc_add(a, t0), t1), t2), t3);
 }
+template <bool SUB>
+__device__ __forceinline__ double quad_fold(double a, double t)
+{
+    t = acc_add(t, quad_xor<1>(t));
+    t = acc_add(t, quad_xor<2>(t));
+    return SUB ? acc_sub(a, t) : acc_add(a, t);
+}
+// Whether the backward sweeps sum the ghosts' terms by themselves and take them
+// off the cell's increment first (they need only that, so the group sweep does
+// it before the chunk's turn); in FP32 they are summed in lane order with the
+// others, chosen by the lane's entry, and with the Roe operator, whose terms
+// take the registers, formed in the turn.
+template <typename T, bool ROE>
+constexpr bool GHOSTS_AHEAD = std::is_same_v<T, double> && !ROE;
 
 // ---- Roe-matrix LU-SGS operator (option lusgs_op = 1 or 2) ----
 // The dissipation of the first-order Roe flux (Eq.18) in place of the
@@ -1985,7 +2013,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
     const int ovf = (quad_get<3>(fl0) & CF_POLY) ? P.covf[c] : -1;   // a polygon's overflow block, or -1
     const T odt = over_cfl(T(quad_get<3>(rp.y)), cfl, icfl);
     const T D = odt + T(quad_get<2>(rp.y)), sadiag = T(quad_get<3>(rp.x));
-    T dws[5], acc[5], t[5];
+    T dws[5], acc[5], gsum[5], t[5];
     if (MODE == SW_FWD || MODE == SW_TOP) {
         acc[0] = T(quad_get<0>(rp.x)); acc[1] = T(quad_get<0>(rp.y));
         acc[2] = T(quad_get<1>(rp.x)); acc[3] = T(quad_get<1>(rp.y));
@@ -2024,12 +2052,19 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
         for (int k = 0; k < 5; k++) dws[k] = P.dW[k * N + c];
     }
 #pragma unroll
-    for (int k = 0; k < 5; k++) acc[k] = T(0);
+    for (int k = 0; k < 5; k++) acc[k] = gsum[k] = T(0);
     auto upper = [&](int f, int e, int j, int fl) {
 #pragma unroll
         for (int m = 0; m < 5; m++) t[m] = T(0);
         if ((fl & CF_VALID) && !(j >= 0 && (fl & (CF_LOWER | CF_OTHER))))
             sweep_term<T, ROE>(P, ip, W, w, f, e, j, dws, cfl, icfl, lev1, t);
+        if (GHOSTS_AHEAD<T, ROE>) {
+#pragma unroll
+            for (int m = 0; m < 5; m++) {
+                gsum[m] = quad_fold<false>(gsum[m], j < 0 ? t[m] : T(0));
+                t[m] = j < 0 ? T(0) : t[m];
+            }
+        }
 #pragma unroll
         for (int m = 0; m < 5; m++) acc[m] = quad_fold<false>(acc[m], t[m]);
     };
@@ -2038,6 +2073,12 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
         upper(P.cf_face[MAXV * ovf + q], MAXV * ovf + q, P.cf_nbr[MAXV * ovf + q], P.cf_flag[MAXV * ovf + q]);
     if (q != 0) return 0.0;
     T d[5];
+    if (GHOSTS_AHEAD<T, ROE>) {
+        const T iD = inv(D);
+#pragma unroll
+        for (int k = 0; k < 4; k++) dws[k] = fma(-gsum[k], iD, dws[k]);
+        if (ip.sa) dws[4] = acc_add(dws[4], SaDiag<T>(odt + sadiag).solve(gsum[4]));
+    }
     if (ROE) {
         T y[4];
         dinv_apply(P, c, acc, y);
@@ -2049,8 +2090,11 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
         for (int k = 0; k < 4; k++) d[k] = dws[k] - acc[k] * iD;
     }
     d[4] = ip.sa ? acc_add(dws[4], SaDiag<T>(odt + sadiag).solve(acc[4])) : T(0);
+    // nothing reads the final increments of the first wavefront
+    if (c >= lev1) {
 #pragma unroll
-    for (int k = 0; k < 5; k++) P.dW[k * N + c] = d[k];
+        for (int k = 0; k < 5; k++) P.dW[k * N + c] = d[k];
+    }
     double dd[5];
 #pragma unroll
     for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
@@ -2058,8 +2102,11 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
 }
 
 // One wavefront of cells [c0, c1), four lanes per cell (sweep_quad)
+// Held to 96 registers (five waves per SIMD) where that spills only on a
+// polygon's path: backward on 983k cells 92 -> 83 us; the variant for several
+// instances, which spills more, 117 us and 171 held to it (16 instances of 19k).
 template <typename T, int MODE, bool ONE, bool ROE>
-__global__ __launch_bounds__(256) void k_sweep(Params<T> P, int c0, int c1, int lev1)
+__global__ __launch_bounds__(256, ROE || !ONE ? 1 : 5) void k_sweep(Params<T> P, int c0, int c1, int lev1)
 {
     const int t = xcd_block() * blockDim.x + threadIdx.x;
     const int c = c0 + (t >> 2);
@@ -2094,13 +2141,16 @@ __global__ __launch_bounds__(256) void k_sweep(Params<T> P, int c0, int c1, int 
 //
 // Measured (forward + backward sweep with the update, us), against a wave per
 // block that loaded everything in its turn: 64x32 plate in blocks of 128,
-// 92 -> 36; turbulent plate (100 wavefronts a block) 388 -> 105; 41k aerofoil
-// in blocks of 256, FP32, 119 -> 42; 250k aerofoil, two passes, 745 -> 186;
+// 92 -> 31; turbulent plate (100 wavefronts a block) 388 -> 83; 41k aerofoil
+// in blocks of 256, FP32, 119 -> 42; 250k aerofoil, two passes, 745 -> 178;
 // against one workgroup with a barrier after each wavefront: the polygon
-// cavity in its own order (385 wavefronts) 1940 -> 467.  Where wavefronts are
-// single chunks the chain bounds it, 0.4 us a forward wavefront: its
-// instructions (95 FP64 and lane moves at 4 or more cycles) are half and its
-// two LDS trips most of the rest.  Where several groups share a CU or
+// cavity in its own order (385 wavefronts) 1940 -> 398.  Where wavefronts are
+// single chunks the chain bounds it, 0.35 us a wavefront: its instructions
+// (about 70 FP64 and lane moves at 4 or more cycles) are half and its two LDS
+// trips most of the rest.  The ghosts' terms of the backward sweep are formed
+// ahead of the turn (turbulent plate, backward 62 -> 54 us with four waves),
+// and the state that the update needs is loaded there and not with the
+// chunk's other data, so that nothing spills (16 spilled registers: 64 us).  Where several groups share a CU or
 // wavefronts have several chunks the CU's memory pipe does (its data unit was
 // 90 % busy on the polygon cavity, at about 20 cache lines an instruction), so
 // a cell's residual and diagonal are one 64-byte record that the quad reads
@@ -2160,14 +2210,13 @@ enum { SRC_NONE = 0, SRC_NEAR = 1, SRC_CROSS = 2, SRC_GHOST = 3 };
 template <typename T, int KIND, bool ROE>
 struct ChunkRaw {
     static constexpr bool FWD = grp_fwd(KIND);
-    static constexpr bool OWN = ROE || KIND == GRP_BWD_UPDATE;   // the cell's own state is needed
     using Rec = std::conditional_t<FWD, double, T>;
     int src, bc, slot_j;   // src: SRC_*
     bool poly;             // the quad's cell has entries beyond the fourth
     double w[5], nx, ny, S, lam, sak;
     Rec rx, ry;            // pair q of the cell's record: crec, or the forward sweep's srec
     T dx[KIND == GRP_FWD2 ? 5 : 1];   // a first block pass's increment of the neighbour
-    double wc[OWN ? 5 : 1];
+    double wc[ROE ? 5 : 1];
     T di[ROE ? 4 : 1];     // row q of the cell's inverted diagonal block
 };
 // what the chunks of a group share
@@ -2262,7 +2311,7 @@ __device__ __forceinline__ void chunk_gather(const Params<T> &P, const GroupRun<
         const T2 v = at(reinterpret_cast<const T2 *>(P.srec + r0), (unsigned)sizeof(T) * p);
         R.rx = v.x; R.ry = v.y;
     }
-    if constexpr (ChunkRaw<T, KIND, ROE>::OWN) {
+    if constexpr (ROE) {
 #pragma unroll
         for (int k = 0; k < 5; k++) R.wc[k] = at(G.W + k * N + I.c0, o);
     }
@@ -2325,18 +2374,22 @@ __device__ __forceinline__ void entry_incr(const Params<T> &P, const ChunkRaw<T,
         }
     }
 }
-// the term: with that increment, that of the first block pass, or the ghost's
-// (wall speed vw) from the cell's own
+// the term: with that increment or that of the first block pass; a ghost's tg,
+// or (Roe) from the cell's own increment and the wall speed vw
 template <typename T, int KIND, bool ROE>
 __device__ __forceinline__ void entry_term(const ChunkRaw<T, KIND, ROE> &R, const TermCoef<T, ROE> &C, const T *dws,
-                                           T vw, T *d, T *t)
+                                           T vw, const T *tg, T *d, T *t)
 {
     if constexpr (KIND == GRP_FWD2) {
 #pragma unroll
         for (int k = 0; k < 5; k++) d[k] = R.src == SRC_CROSS ? R.dx[k] : d[k];
     }
-    if (!grp_fwd(KIND) && R.src == SRC_GHOST) ghost_incr<T>(R.bc, dws, C.jac.nx, C.jac.ny, vw, d);
+    if (ROE && !grp_fwd(KIND) && R.src == SRC_GHOST) ghost_incr<T>(R.bc, dws, C.jac.nx, C.jac.ny, vw, d);
     term_apply<T, ROE>(C, d, t);
+    if constexpr (!ROE && !grp_fwd(KIND) && !GHOSTS_AHEAD<T, ROE>) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) t[k] = R.src == SRC_GHOST ? tg[k] : t[k];
+    }
 }
 
 // Chunk i of the wave (loaded: A): the next chunk's loads into Rn (entries
@@ -2379,9 +2432,37 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
     for (int k = 0; k < 5; k++) pin(rhs[k]);
     pin(iD);
     pin(Ds.v);
-    T vw = T(0), vwB = T(0);
-    if (!FWD && A.src == SRC_GHOST && A.bc == BC_MOVING_WALL) vw = T(wall_speed(ip, A.nx, A.ny));
-    pin(vw);
+    // the ghosts' terms, which follow from the cell's own increment: their
+    // sum (gsum) or each lane's own (tg); with the Roe operator only the wall
+    // speed they need (vw)
+    constexpr bool AHEAD = GHOSTS_AHEAD<T, ROE>;
+    T gsum[5], tg[5], tgB[5], vw = T(0), vwB = T(0);
+    auto ghost_terms = [&](const ChunkRaw<T, KIND, ROE> &R, TermCoef<T, ROE> &Cr, T *tr, T &v) {
+        const bool gh = !FWD && R.src == SRC_GHOST;
+        if constexpr (!FWD && ROE) {
+            if (gh && R.bc == BC_MOVING_WALL) v = T(wall_speed(ip, R.nx, R.ny));
+            pin(v);
+        } else if constexpr (!FWD) {
+#pragma unroll
+            for (int k = 0; k < 5; k++) tr[k] = T(0);
+            if (__any(gh)) {
+                if (gh) {
+                    T dg[5];
+                    ghost_incr<T>(R.bc, rhs, Cr.jac.nx, Cr.jac.ny, T(wall_speed(ip, R.nx, R.ny)), dg);
+                    term_apply<T, ROE>(Cr, dg, tr);
+                }
+#pragma unroll
+                for (int k = 0; k < 5; k++)
+                    if (AHEAD) gsum[k] = quad_fold<false>(gsum[k], tr[k]);
+            }
+            if (AHEAD) no_term(Cr, gh);
+#pragma unroll
+            for (int k = 0; k < 5; k++) pin(AHEAD ? gsum[k] : tr[k]);
+        }
+    };
+#pragma unroll
+    for (int k = 0; k < 5; k++) gsum[k] = T(0);
+    ghost_terms(A, C, tg, vw);
     // the entries of polygons beyond the fourth, formed ahead too unless the
     // Roe matrices take the registers
     ChunkRaw<T, KIND, ROE> B;
@@ -2399,9 +2480,23 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
         CB = entry_coef<T, KIND, ROE>(P, ip, B);
         no_term(CB, B.src == SRC_NONE);
         pin_coef(CB);
-        if (!FWD && B.src == SRC_GHOST && B.bc == BC_MOVING_WALL) vwB = T(wall_speed(ip, B.nx, B.ny));
+        ghost_terms(B, CB, tgB, vwB);
     };
     if (!ROE && poly) overflow();
+    if constexpr (!FWD && AHEAD) {
+#pragma unroll
+        for (int k = 0; k < 4; k++) rhs[k] = fma(-gsum[k], iD, rhs[k]);
+        if (sa) rhs[4] = acc_add(rhs[4], Ds.solve(gsum[4]));
+#pragma unroll
+        for (int k = 0; k < 5; k++) pin(rhs[k]);
+    }
+    // what only the update needs is loaded here, into registers that the
+    // ghosts and the polygons' entries needed
+    double wu[KIND == GRP_BWD_UPDATE && !ROE ? 5 : 1];
+    if constexpr (KIND == GRP_BWD_UPDATE && !ROE) {
+#pragma unroll
+        for (int k = 0; k < 5; k++) wu[k] = at(G.W + k * N + c0, 8u * (unsigned)dc);
+    }
     // its turn: every chunk of the earlier wavefronts is complete.  The LDS
     // executes a wave's operations in order, so the increments read after
     // the count are at least as new as it, and the count is raised after the
@@ -2431,7 +2526,7 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         entry_incr<T, KIND, RING, ROE>(P, A, G.dw, d);
     }
-    entry_term<T, KIND, ROE>(A, C, rhs, vw, d, t);
+    entry_term<T, KIND, ROE>(A, C, rhs, vw, tg, d, t);
     if (FWD) {
         // M less the lower neighbours' terms
 #pragma unroll
@@ -2444,7 +2539,7 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
     if (poly) {
         if (ROE) overflow();
         entry_incr<T, KIND, RING, ROE>(P, B, G.dw, d);
-        entry_term<T, KIND, ROE>(B, CB, rhs, vwB, d, t);
+        entry_term<T, KIND, ROE>(B, CB, rhs, vwB, tgB, d, t);
 #pragma unroll
         for (int m = 0; m < 4; m++) acc[m] = quad_fold<FWD>(acc[m], t[m]);
         acc[4] = quad_fold<false>(acc[4], t[4]);
@@ -2485,7 +2580,7 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
             double dd[5];
 #pragma unroll
             for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
-            e40 = apply_update(P, c0 + dc, G.inst, sa, G.Wn, A.wc, dd);
+            e40 = apply_update(P, c0 + dc, G.inst, sa, G.Wn, ROE ? A.wc : wu, dd);
         }
     } else if constexpr (FWD) {
         // for the backward sweep: a pair of values from each lane of the quad
