@@ -1796,7 +1796,7 @@ struct SaDiag {
 
 // Forward-sweep increment dW*_j of a cell of the first wavefront: it has no
 // lower neighbours, so Eq.22 reduces to dW*_j = D_j^-1 M_j (the expressions
-// of sweep_cell with nothing subtracted, hence the same numbers).  Formed
+// of a forward step with nothing subtracted, hence the same numbers).  Formed
 // where it is needed instead of in a launch of its own.
 template <typename T, bool ROE>
 __device__ __forceinline__ void first_front_incr(const Params<T> &P, const InstParam &ip, int j, T cfl, T icfl, T *d)
@@ -1990,7 +1990,7 @@ __global__ __launch_bounds__(256) void k_explicit(Params<T> P)
 // A cell takes a quad of lanes (q = 0..3, one cell per aligned quad): lane
 // q takes entry q of each of the cell's entry blocks, so a cell's neighbour
 // terms are formed side by side instead of one after another, and the
-// terms are combined on every lane of the quad in entry order (quad_fold).
+// terms are combined on every lane of the quad, the same on each (quad_fold).
 // Lane 0 stores and returns the Eq.40 ratio; the other lanes return 0.
 // Cells below lev1 (the first wavefront) have no stored forward increment:
 // their own and their neighbours' are formed by first_front_incr.
