@@ -703,11 +703,16 @@ template <typename V>
 struct JacCoef {
     V nx, ny, m1, m2, ir, u, v, q, ke, ep;   // normal, momentum, 1/rho, velocity, V.n, |V|^2/2, rho E + p
 };
-// 1/x for the sweeps: in FP64 the refined hardware reciprocal (five
+// 1/x for the sweeps: in FP64 the refined hardware reciprocal (six
 // instructions; the divide's eleven were a tenth of what a wave of the group
-// sweep issues), in FP32 the divide.
-__device__ __forceinline__ double inv(double x) { return frcp(x); }
+// sweep issues), in FP32 the divide.  The last one mends the reciprocals of 0
+// and of infinity, whose refinement is NaN: the CFL number may be either (an
+// unbounded step, none), and the diagonal is infinite where it is 0.
+__device__ __forceinline__ double inv(double x) { return __builtin_amdgcn_div_fixup(frcp(x), x, 1.0); }
 __device__ __forceinline__ float inv(float x) { return 1.0f / x; }
+// 1/rho (positive and finite)
+__device__ __forceinline__ double inv_rho(double x) { return frcp(x); }
+__device__ __forceinline__ float inv_rho(float x) { return 1.0f / x; }
 // Omega / dt_imp = Lambda_c / CFL (Eq.24), icfl = 1 / CFL used in FP64 only
 // (a product of its own, never fused into the diagonal's sum)
 __device__ __forceinline__ double over_cfl(double lamc, double, double icfl)
@@ -724,7 +729,7 @@ __device__ __forceinline__ JacCoef<V> jac_coef(const V *W, V nx, V ny)
     JacCoef<V> c;
     const V r = W[0], E = W[3];
     c.nx = nx; c.ny = ny; c.m1 = W[1]; c.m2 = W[2];
-    c.ir = inv(r);
+    c.ir = inv_rho(r);
     c.u = W[1] * c.ir; c.v = W[2] * c.ir;
     c.ke = V(0.5) * fma(c.u, c.u, c.v * c.v);
     c.ep = fma(V(GAMMA - 1.0), fma(-r, c.ke, E), E);
