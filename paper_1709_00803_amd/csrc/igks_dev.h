@@ -178,8 +178,8 @@ struct SweepGroups {
     // group's increments stay in global memory); chunks of earlier (forward) and of later wavefronts
     const int4 *chunk;
 };
-// LDS of a group's ring and its count of finished chunks
-constexpr size_t grp_lds(int slots, size_t size) { return 5 * size * (size_t)slots + 16; }
+// LDS of a group's ring, a slot of zeros and its count of finished chunks
+constexpr size_t grp_lds(int slots, size_t size) { return 5 * size * (size_t)(slots + 1) + 16; }
 // the whole forward or backward sweep, one launch; `update`: the last backward
 // sweep, which also updates every cell
 template <typename T>

@@ -2267,10 +2267,10 @@ __device__ __forceinline__ int entry_source(int j, int fl)
     return (fl & (CF_LOWER | CF_OTHER)) ? SRC_NONE : SRC_NEAR;
 }
 // the loads of one entry's term, its geometry at element e of the arrays from
-// e0 on (a ghost's state follows from the cell's)
+// e0 on (a ghost's state follows from the cell's); on: the lane has this entry
 template <typename T, int KIND, bool RING, bool ROE>
 __device__ __forceinline__ void entry_gather(const Params<T> &P, const GroupRun<T> &G, int c, size_t e0, unsigned e,
-                                             int f, int j, int fl, ChunkRaw<T, KIND, ROE> &R)
+                                             int f, int j, int fl, bool on, ChunkRaw<T, KIND, ROE> &R)
 {
     const size_t N = P.nc;
     R.src = entry_source<KIND>(j, fl);
@@ -2290,7 +2290,8 @@ __device__ __forceinline__ void entry_gather(const Params<T> &P, const GroupRun<
         const int fb = R.src == SRC_GHOST ? f : __builtin_amdgcn_readfirstlane(f);
         R.bc = at(P.fbc, 4u * (unsigned)fb);
     }
-    R.slot_j = RING ? (R.src == SRC_NEAR ? fl >> CF_SLOT_SHIFT : 0) : jw;
+    R.src = on ? R.src : SRC_NONE;
+    R.slot_j = RING ? (R.src == SRC_NEAR ? fl >> CF_SLOT_SHIFT : G.slots) : jw;
     if constexpr (KIND == GRP_FWD2) {
 #pragma unroll
         for (int k = 0; k < 5; k++) R.dx[k] = at(P.dWx + k * N, (unsigned)sizeof(T) * (unsigned)jw);
@@ -2303,8 +2304,7 @@ __device__ __forceinline__ void chunk_gather(const Params<T> &P, const GroupRun<
     const size_t N = P.nc;
     const int q = G.q;
     entry_gather<T, KIND, RING, ROE>(P, G, I.c0 + I.dc, (size_t)MAXV * I.c0, (unsigned)(MAXV * I.dc + q), I.f, I.j,
-                                     I.fl, R);
-    if (!I.act) R.src = SRC_NONE;
+                                     I.fl, I.act, R);
     R.poly = I.act && (quad_get<3>(I.fl) & CF_POLY);
     const unsigned o = 8u * (unsigned)I.dc, p = (unsigned)(CR_STRIDE * I.dc + 2 * q);
     const size_t r0 = (size_t)CR_STRIDE * I.c0;
@@ -2354,9 +2354,9 @@ __device__ __forceinline__ void pin_coef(TermCoef<T, ROE> &C)
         pin(C.R.m0); pin(C.R.m1); pin(C.R.m3); pin(C.R.ic); pin(C.R.g1c2);
     }
 }
-// An entry that has no term here gets the coefficients 0: its slot holds a
-// finite increment (the ring starts at 0), or a non-finite one of an update
-// that is going to be rejected.
+// An entry that has no term here gets the coefficients 0 and, from the slot
+// past the ring that nothing writes, the increment 0: another cell's would not
+// do, whose SA component may be infinite (the update clips nu~ at 0).
 template <typename T, bool ROE>
 __device__ __forceinline__ void no_term(TermCoef<T, ROE> &C, bool none)
 {
@@ -2480,8 +2480,8 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
 #pragma unroll
             for (int k = 0; k < 5; k++) B.wc[k] = A.wc[k];
         }
-        entry_gather<T, KIND, RING, ROE>(P, G, c, e, 0u, P.cf_face[e], P.cf_nbr[e], P.cf_flag[e], B);
-        if (!A.poly) B.src = SRC_NONE;
+        entry_gather<T, KIND, RING, ROE>(P, G, c, e, 0u, P.cf_face[e], P.cf_nbr[e], P.cf_flag[e], A.poly,
+                                         B);
         CB = entry_coef<T, KIND, ROE>(P, ip, B);
         no_term(CB, B.src == SRC_NONE);
         pin_coef(CB);
@@ -2625,8 +2625,8 @@ __device__ __forceinline__ double group_sweep(const Params<T> &P, const InstPara
 // chunk[ch_off[g] .. ch_off[g + 1]): the group's chunks in forward order.  A
 // group whose couplings span more cells than the ring holds (slot -1) passes
 // its increments through global memory instead (all_ring: no such group).
-// Dynamic LDS: the ring of `slots` increments, then the count of finished
-// chunks.
+// Dynamic LDS: the ring of `slots` increments, one more that stays 0, then the
+// count of finished chunks.
 template <typename T, int KIND, bool ONE, bool ROE>
 __global__ __launch_bounds__(64 * (ROE ? GRP_WAVES_ROE : GRP_WAVES)) void k_sweep_grp(
     Params<T> P, const int *ch_off, const int4 *chunk, int slots, int all_ring)
@@ -2634,7 +2634,7 @@ __global__ __launch_bounds__(64 * (ROE ? GRP_WAVES_ROE : GRP_WAVES)) void k_swee
     extern __shared__ __align__(16) unsigned char smem[];
     GroupRun<T> G;
     G.dw = reinterpret_cast<T *>(smem);
-    G.done = reinterpret_cast<unsigned *>(smem + sizeof(T) * 5 * (size_t)slots);
+    G.done = reinterpret_cast<unsigned *>(smem + sizeof(T) * 5 * (size_t)(slots + 1));
     const int k0 = ch_off[blockIdx.x];
     G.n = ch_off[blockIdx.x + 1] - k0;
     if (G.n <= 0) return;
@@ -2652,7 +2652,7 @@ __global__ __launch_bounds__(64 * (ROE ? GRP_WAVES_ROE : GRP_WAVES)) void k_swee
     G.q = lane & 3;
     G.cell = lane >> 2;
     G.nw = (int)blockDim.x >> 6;
-    for (int k = threadIdx.x; k < 5 * slots; k += blockDim.x) G.dw[k] = T(0);
+    for (int k = threadIdx.x; k < 5 * (slots + 1); k += blockDim.x) G.dw[k] = T(0);
     if (threadIdx.x == 0) *G.done = 0u;
     __syncthreads();
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
