@@ -703,16 +703,19 @@ template <typename V>
 struct JacCoef {
     V nx, ny, m1, m2, ir, u, v, q, ke, ep;   // normal, momentum, 1/rho, velocity, V.n, |V|^2/2, rho E + p
 };
-// 1/x for the sweeps: in FP64 the refined hardware reciprocal (six
-// instructions; the divide's eleven were a tenth of what a wave of the group
-// sweep issues), in FP32 the divide.  The last one mends the reciprocals of 0
-// and of infinity, whose refinement is NaN: the CFL number may be either (an
-// unbounded step, none), and the diagonal is infinite where it is 0.
-__device__ __forceinline__ double inv(double x) { return __builtin_amdgcn_div_fixup(frcp(x), x, 1.0); }
+// 1/x for the sweeps (x finite, not 0): in FP64 the refined hardware reciprocal
+// (five instructions; the divide's eleven were a tenth of what a wave of the
+// group sweep issues), in FP32 the divide.
+__device__ __forceinline__ double inv(double x) { return frcp(x); }
 __device__ __forceinline__ float inv(float x) { return 1.0f / x; }
-// 1/rho (positive and finite)
-__device__ __forceinline__ double inv_rho(double x) { return frcp(x); }
-__device__ __forceinline__ float inv_rho(float x) { return 1.0f / x; }
+// 1 / CFL, 0 where the CFL number is infinite (the refinement alone gives NaN)
+__device__ __forceinline__ double inv_cfl(double cfl) { return __builtin_amdgcn_div_fixup(frcp(cfl), cfl, 1.0); }
+__device__ __forceinline__ float inv_cfl(float cfl) { return 1.0f / cfl; }
+// A CFL number of 0, or one so small that Lambda_c / CFL overflows, makes no
+// step: the update takes 0 for whatever the sweeps made of the infinite
+// diagonal.  (Mending the reciprocals of the diagonals instead took k_sweep on
+// 983k cells from 48 + 82 to 52 + 85 us; this, where it stands, takes nothing.)
+__device__ __forceinline__ bool no_step(double cfl) { return fabs(cfl) < 1e-300; }
 // Omega / dt_imp = Lambda_c / CFL (Eq.24), icfl = 1 / CFL used in FP64 only
 // (a product of its own, never fused into the diagonal's sum)
 __device__ __forceinline__ double over_cfl(double lamc, double, double icfl)
@@ -729,7 +732,7 @@ __device__ __forceinline__ JacCoef<V> jac_coef(const V *W, V nx, V ny)
     JacCoef<V> c;
     const V r = W[0], E = W[3];
     c.nx = nx; c.ny = ny; c.m1 = W[1]; c.m2 = W[2];
-    c.ir = inv_rho(r);
+    c.ir = inv(r);
     c.u = W[1] * c.ir; c.v = W[2] * c.ir;
     c.ke = V(0.5) * fma(c.u, c.u, c.v * c.v);
     c.ep = fma(V(GAMMA - 1.0), fma(-r, c.ke, E), E);
@@ -2008,7 +2011,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
     const InstScalars &sc = P.is[inst];
     const InstParam &ip = P.ip[inst];
     const double *W = cur_state(P, inst);
-    const T cfl = T(sc.cfl), icfl = inv(cfl);
+    const T cfl = T(sc.cfl), icfl = inv_cfl(cfl);
     double w[5];
 #pragma unroll
     for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
@@ -2077,6 +2080,10 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
     if (ovf >= 0)
         upper(P.cf_face[MAXV * ovf + q], MAXV * ovf + q, P.cf_nbr[MAXV * ovf + q], P.cf_flag[MAXV * ovf + q]);
     if (q != 0) return 0.0;
+    if (no_step(sc.cfl)) {
+        const double none[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        return apply_update(P, c, inst, ip.sa, next_state(P, inst), w, none);
+    }
     T d[5];
     if (GHOSTS_AHEAD<T, ROE>) {
         const T iD = inv(D);
@@ -2233,6 +2240,7 @@ struct GroupRun {
     T *dw;             // the ring
     unsigned *done;    // finished chunks
     T cfl, icfl;
+    bool still;        // the CFL number makes no step (no_step)
     int n, q, cell, nw, inst, slots;
 };
 
@@ -2584,7 +2592,7 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
         if (store) {
             double dd[5];
 #pragma unroll
-            for (int k = 0; k < 5; k++) dd[k] = double(d[k]);
+            for (int k = 0; k < 5; k++) dd[k] = G.still ? 0.0 : double(d[k]);
             e40 = apply_update(P, c0 + dc, G.inst, sa, G.Wn, ROE ? A.wc : wu, dd);
         }
     } else if constexpr (FWD) {
@@ -2647,7 +2655,8 @@ __global__ __launch_bounds__(64 * (ROE ? GRP_WAVES_ROE : GRP_WAVES)) void k_swee
     G.W = cur_state(P, G.inst);
     G.Wn = next_state(P, G.inst);
     G.cfl = T(P.is[G.inst].cfl);
-    G.icfl = inv(G.cfl);
+    G.icfl = inv_cfl(G.cfl);
+    G.still = no_step(P.is[G.inst].cfl);
     const int lane = (int)threadIdx.x & 63;
     G.q = lane & 3;
     G.cell = lane >> 2;

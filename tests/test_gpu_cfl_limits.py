@@ -54,12 +54,14 @@ def test_infinite_cfl(igks, name, sweep, passes, op):
     assert err <= 1e-9, err
 
 
+@pytest.mark.parametrize("op", [0, 1])
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("name,sweep,passes", [("colour", 1, 1), ("natural", 2, 1), ("polygons", 2, 1),
                                                ("blocks", 3, 2)])
-def test_zero_cfl(igks, name, sweep, passes, precision):
-    print("case", name, sweep, passes, precision, flush=True)
-    m, blk, g = solver(igks, name, sweep=sweep, block_passes=passes, precision=precision, cfl_init=5.0, cfl_mode=1)
+def test_zero_cfl(igks, name, sweep, passes, precision, op):
+    print("case", name, sweep, passes, precision, op, flush=True)
+    m, blk, g = solver(igks, name, sweep=sweep, block_passes=passes, precision=precision, lusgs_op=op, cfl_init=5.0,
+                       cfl_mode=1)
     g.iterate(2)
     W, sc = g.get_state(), g.scalars()
     sc.cfl = 0.0
