@@ -142,6 +142,13 @@ def _mesh_args(mesh):
 KERNEL_CLASSES = ("prep", "flux", "gather", "reduce", "sweep_fwd", "sweep_bwd")
 
 
+def _entries(max_entries):
+    """The count of history entries to be read, of at most max_entries."""
+    if max_entries < 0:
+        raise ValueError(f"max_entries = {max_entries} is negative")
+    return C.c_int32()
+
+
 class _Context:
     """Owns an igks context, its stream and its device workspace."""
 
@@ -260,7 +267,7 @@ class Solver(_Context):
         return r.as_dict()
 
     def history(self, max_entries=1 << 20):
-        n = C.c_int32()
+        n = _entries(max_entries)
         self._chk(igks_get_history(self.ctx, None, max_entries, C.byref(n)))
         out = np.empty((n.value, HIST_W))
         self._chk(igks_get_history(self.ctx, out.ctypes.data_as(_DP), n.value, C.byref(n)))
@@ -331,7 +338,7 @@ class BatchSolver(_Context):
         return r.as_dict()
 
     def history(self, i, max_entries=1 << 20):
-        n = C.c_int32()
+        n = _entries(max_entries)
         self._chk(igks_batch_get_history(self.ctx, i, None, max_entries, C.byref(n)))
         out = np.empty((n.value, HIST_W))
         self._chk(igks_batch_get_history(self.ctx, i, out.ctypes.data_as(_DP), n.value, C.byref(n)))
