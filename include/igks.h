@@ -351,10 +351,9 @@ int igks_get_schedule(const igks_ctx *ctx, int32_t *schedule6);
  * blocks. */
 int igks_set_schedule(igks_ctx *ctx, const int32_t *schedule6);
 
-/* Iterations per captured HIP graph and kernel launches per iteration (at
- * most) of the current schedule (before binding: of the schedule binding will
- * pick).  A
- * graph holds at most 8192 launches: with one launch per wavefront and sweep
+/* Iterations per captured HIP graph and, at most, kernel launches per iteration
+ * of the current schedule (before binding: of the schedule binding will pick).
+ * A graph holds at most 8192 launches: with one launch per wavefront and sweep
  * direction an iteration of a many-wavefront batch is thousands of launches
  * long, and the chunk is cut to fit; 0 iterations: no graphs (chunk 0).
  * Works without a GPU once every instance has a mesh. */

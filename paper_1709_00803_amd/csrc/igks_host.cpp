@@ -241,14 +241,21 @@ void destroy_graph(igks_ctx *c)
 // launches long); 0 = no graphs.
 constexpr int MAX_GRAPH_NODES = 8192;
 bool two_block_passes(const igks_ctx *c);
+// at most: the commit, counted for every iteration, has a launch of its own
+// after the last of a chunk (after each where the limiter may freeze)
 int launches_per_iteration(const igks_ctx *c, int sweep_mode)
 {
     const int nlev = std::max(1, c->g.nlev);
-    // per-wavefront sweeps: forward steps of wavefronts 1 .. nlev-2, the last
-    // wavefront's two steps, backward steps of nlev-2 .. 0; the group sweeps:
-    // forward, backward, update (a bound: the update rides in the backward sweep)
-    int sweeps = c->opt.scheme == 1 ? 1 : (sweep_mode >= 2 ? 3 : std::max(1, 2 * nlev - 2));
-    if (c->opt.scheme != 1 && sweep_mode == 3 && two_block_passes(c)) sweeps += 2;   // the first pass
+    const bool roe = c->opt.lusgs_op >= 1;   // the inverted diagonal blocks
+    int sweeps = 1;   // the explicit update
+    if (c->opt.scheme != 1) {
+        // per-wavefront sweeps: forward steps of wavefronts 1 .. nlev-2, the
+        // last wavefront's two steps, backward steps of nlev-2 .. 0; the group
+        // sweeps: forward and backward (with the update), counted with the
+        // diagonal blocks whatever the operator
+        sweeps = sweep_mode >= 2 ? 3 : std::max(1, 2 * nlev - 2) + roe;
+        if (sweep_mode == 3 && two_block_passes(c)) sweeps += 2;   // the first pass
+    }
     return 5 + sweeps;   // prep, flux, gather, reduce, commit + the update / sweep launches
 }
 int graph_chunk_for(const igks_ctx *c, int sweep_mode)
