@@ -1910,19 +1910,15 @@ int igks_autotune(igks_ctx *c, int32_t iters, int32_t *s6)
         }
     for (int k = 0; k < NCLASS; k++) c->block[k] = best[k];
     c->flux_pair = rc ? pair_auto : best_pair;
-    // sweeps: one launch per wavefront (timed above), one workgroup per
-    // instance (a candidate only while wavefronts are narrow) or per sweep block
+    // sweeps: one launch per wavefront (timed above), or one workgroup per sweep
+    // block or per instance (schedules 2 and 3, which launch the same: without
+    // sweep blocks a candidate only while wavefronts are narrow)
     int best_mode = two_block_passes(c) ? 3 : 1;   // two passes run on the workgroup-per-block schedule only
-    double best_sweep = best_t[3];
-    for (int mode = 2; mode <= 3 && !rc && !two_block_passes(c); mode++) {
-        if (mode == 2 && !((double)c->g.N / std::max(1, c->g.nlev) < 16384.0)) continue;
-        if (mode == 3 && !any_sweep_blocks(c)) continue;
-        c->sweep_mode = mode;
+    const int group_mode = any_sweep_blocks(c) ? 3 : 2;
+    if (!rc && !two_block_passes(c) && (group_mode == 3 || (double)c->g.N / std::max(1, c->g.nlev) < 16384.0)) {
+        c->sweep_mode = group_mode;
         rc = (c->opt.precision == IGKS_MIXED) ? tune_run(c, c->P32, iters) : tune_run(c, c->P64, iters);
-        if (!rc && c->ktimes[4] + c->ktimes[5] < best_sweep) {
-            best_sweep = c->ktimes[4] + c->ktimes[5];
-            best_mode = mode;
-        }
+        if (!rc && c->ktimes[4] + c->ktimes[5] < best_t[3]) best_mode = group_mode;
     }
     c->sweep_mode = rc ? mode_auto : best_mode;
     c->profiling = prof;
