@@ -153,8 +153,8 @@ typedef struct igks_ctx igks_ctx;
 /* Fill *opt with the defaults: FP64, limiter off, cfl_init 1000 (Sec. 3.1),
  * cfl_min 1, cfl_max 1e6, Eq.25 law, cfl_flux 1, visc_sr on, Sutherland,
  * chunk 20, block 256, sweep auto (a workgroup per sweep block when an instance has
- * sweep blocks, else one per instance when the wavefronts are many and narrow:
- * more than 16 of them averaging under 1024 cells), flux_lanes auto. */
+ * sweep blocks, else one per instance when there are more than 16 wavefronts, in
+ * the largest instance of about 480 cells or fewer on average), flux_lanes auto. */
 void igks_default_options(igks_options *opt);
 
 /* Create a context.  opt may be NULL (defaults).  hip_stream is a

@@ -91,8 +91,9 @@ struct Params {
     // line: the residual (4 flow components, SA right-hand side), 1/2 sum
     // lambda S (Eq.20 diagonal), the SA diagonal without Omega/dt, Lambda_c
     double *crec;
-    T *srec;                   // the same shape from the forward to the backward group sweep:
-                               // dW*, 1 / D, the SA diagonal (in the gradients' memory)
+    T *srec;                   // the same shape from the forward to the backward group sweep (dW*,
+                               // 1 / D, the SA diagonal) and from there to the update (dW); in the
+                               // gradients' memory
     double *r2;                // squares for the norms, M_rho^2 then R_SA^2, at the cell's ipos
     T *dW;                     // LU-SGS increment, 5 x nc
     const T *dWx;              // a first block pass's increments, whose cross-block terms the
@@ -173,6 +174,7 @@ struct SweepGroups {
     int n;                              // groups
     int slots, waves;                   // LDS slots, waves per group
     bool all_ring;                      // every group's increments fit the ring
+    bool split_update;                  // the update in a launch of its own
     const int *ch_off;                  // group g's chunks: [ch_off[g], ch_off[g + 1])
     // per chunk: first cell; cells | (LDS slot of the first + 1) << CH_SLOT_SHIFT (slot -1: the
     // group's increments stay in global memory); chunks of earlier (forward) and of later wavefronts
@@ -181,7 +183,7 @@ struct SweepGroups {
 // LDS of a group's ring, a slot of zeros and its count of finished chunks
 constexpr size_t grp_lds(int slots, size_t size) { return 5 * size * (size_t)(slots + 1) + 16; }
 // the whole forward or backward sweep, one launch; `update`: the last backward
-// sweep, which also updates every cell
+// sweep, which also updates every cell, in it or after it (split_update)
 template <typename T>
 void launch_sweep_grp(const Launch &L, const Params<T> &P, const SweepGroups &G, bool fwd, bool update);
 // mail: null, or host memory (mapped) for the scalars of all instances and

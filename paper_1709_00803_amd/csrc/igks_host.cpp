@@ -56,8 +56,8 @@ struct Global {
     std::vector<int> ch_off, cslot;
     std::vector<int> covf;           // overflow block of each cell, -1: none (empty: no polygons)
     std::vector<int4> chunk;
-    int grp_slots = 0, grp_waves = 4;
-    bool grp_all_ring = true;
+    int grp_slots = 0, grp_waves = 4, grp_chunks = 0;   // grp_chunks: of the largest group
+    bool grp_all_ring = true, grp_split_update = false;
     std::vector<int> coff;           // first global upload id of each instance
     std::vector<int> g2i;            // global upload id -> internal cell
     std::vector<int> cinst, finst, icell, ioff, ipos, cperm;
@@ -251,9 +251,9 @@ int launches_per_iteration(const igks_ctx *c, int sweep_mode)
     if (c->opt.scheme != 1) {
         // per-wavefront sweeps: forward steps of wavefronts 1 .. nlev-2, the
         // last wavefront's two steps, backward steps of nlev-2 .. 0; the group
-        // sweeps: forward and backward (with the update), counted with the
-        // diagonal blocks whatever the operator
-        sweeps = sweep_mode >= 2 ? 3 : std::max(1, 2 * nlev - 2) + roe;
+        // sweeps: forward, backward, update (counted whether or not the
+        // backward sweep has it in it, unless the diagonal blocks take its place)
+        sweeps = sweep_mode >= 2 ? std::max(3, 2 + c->g.grp_split_update + roe) : std::max(1, 2 * nlev - 2) + roe;
         if (sweep_mode == 3 && two_block_passes(c)) sweeps += 2;   // the first pass
     }
     return 5 + sweeps;   // prep, flux, gather, reduce, commit + the update / sweep launches
@@ -266,11 +266,15 @@ int graph_chunk_for(const igks_ctx *c, int sweep_mode)
 int graph_chunk(const igks_ctx *c) { return graph_chunk_for(c, c->sweep_mode); }
 
 // The schedule chosen at binding time from the sizes: one workgroup per
-// instance for the sweeps when wavefronts are many and narrow (a workgroup
-// takes 0.4 to 1 us a wavefront of up to a hundred cells, a launch 4 us or
-// more); one lane per face (its kernel holds two waves per SIMD and executes
-// the fewest instructions per face) except on small meshes, where two lanes
-// per face give the SIMDs twice as many waves to switch between.
+// instance for the sweeps when wavefronts are many and, in the largest
+// instance, narrow.  A wavefront of both sweeps costs such a workgroup 0.7 us
+// and 0.31 us a chunk of 16 cells, the launches 9 to 10 us: with wavefronts of
+// 188 cells an iteration takes 3.6 ms against 8.2 launched, of 375 14.7 against
+// 19.5, of 525 28.9 against 28.1, of 750 61 against 41; 8 instances in
+// wavefronts of 150 3.3 against 9.3 ms (more than 256 of them share the CUs).
+// One lane per face (its kernel holds two waves per SIMD and executes the
+// fewest instructions per face) except on small meshes, where two lanes per
+// face give the SIMDs twice as many waves to switch between.
 //
 // With sweep blocks the cells of different blocks never wait for each other,
 // so one workgroup sweeps each block on its own (no launch per wavefront, no
@@ -287,8 +291,8 @@ int auto_sweep_mode(const igks_ctx *c)
 {
     if (c->opt.sweep > 0) return c->opt.sweep;
     if (any_sweep_blocks(c)) return 3;
-    const double width = (double)c->g.N / std::max(1, c->g.nlev);
-    return (c->g.nlev > 16 && width < 1024.0) ? 2 : 1;
+    const int per_cu = ((int)c->g.ch_off.size() - 1 + 255) / 256;
+    return (c->g.nlev > 16 && (double)c->g.grp_chunks * per_cu < 30.0 * c->g.nlev) ? 2 : 1;
 }
 bool auto_flux_pair(const igks_ctx *c) { return c->opt.flux_lanes == 2 || (c->opt.flux_lanes == 0 && c->g.F < 32768); }
 
@@ -554,7 +558,7 @@ void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vecto
     }
     G.ch_off.assign(ngb + 1, 0);
     G.chunk.clear();
-    size_t nfronts = 0;
+    size_t nfronts = 0, most = 0, spare = 0;
     for (int b = 0; b < ngb; b++) {
         const size_t k0 = G.chunk.size();
         for (auto &p : rng[b]) {
@@ -573,7 +577,19 @@ void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vecto
         }
         nfronts += rng[b].size();
         G.ch_off[b + 1] = (int)G.chunk.size();
+        most = std::max(most, G.chunk.size() - k0);
+        spare = std::max(spare, G.chunk.size() - k0 - rng[b].size());
     }
+    G.grp_chunks = (int)most;
+    // Where a group has several chunks in a wavefront its waves are always busy,
+    // and each of these chunks costs about 0.045 us more with the update in it; as
+    // a launch of its own the update costs 5 us and the passes over all cells.
+    // Backward sweep with the update in it / after it, us: 100x100 cavity in
+    // natural order 165 / 133, turbulent plate 149 / 125, polygon cavity 209 / 192,
+    // 64x32 plate 51 / 50, 30x30 cavity 31 / 33; 750k cells in wavefronts of 375
+    // 10170 / 7370; wavefronts of 75 in 8 instances 472 / 382, in 64 509 / 510, in
+    // 128 535 / 677; 250k aerofoil in 523 blocks 42 / 46.
+    G.grp_split_update = spare > 80 + (size_t)N / 1000;
     // Where the groups fill the CUs, four waves each, one per SIMD, take turns;
     // fewer groups get eight, so that a wave has time for its loads and its
     // update between its turns, and where their wavefronts are wider than a
@@ -909,6 +925,7 @@ SweepGroups groups_of(igks_ctx *c)
     S.slots = c->g.grp_slots;
     S.waves = c->g.grp_waves;
     S.all_ring = c->g.grp_all_ring;
+    S.split_update = c->g.grp_split_update;
     S.ch_off = (const int *)(c->ws + c->w.ch_off.off);
     S.chunk = (const int4 *)(c->ws + c->w.chunk.off);
     return S;

@@ -2178,8 +2178,9 @@ __global__ __launch_bounds__(256, ROE || !ONE ? 1 : 5) void k_sweep(Params<T> P,
 constexpr unsigned SPIN_LIMIT = 1u << 22;
 
 // sweep kinds of the group sweep: forward; forward of a second block pass
-// (cross-block terms from the first); backward; backward with the update
-enum { GRP_FWD = 0, GRP_FWD2 = 1, GRP_BWD = 2, GRP_BWD_UPDATE = 3 };
+// (cross-block terms from the first); backward of the first of two passes;
+// backward with the update; backward that leaves the increments to k_update
+enum { GRP_FWD = 0, GRP_FWD2 = 1, GRP_BWD = 2, GRP_BWD_UPDATE = 3, GRP_BWD_REC = 4 };
 constexpr bool grp_fwd(int kind) { return kind <= GRP_FWD2; }
 
 // Element at byte offset `off` of an array whose address is the same on all
@@ -2595,8 +2596,10 @@ __device__ __forceinline__ double group_chunk(const Params<T> &P, const InstPara
             for (int k = 0; k < 5; k++) dd[k] = G.still ? 0.0 : double(d[k]);
             e40 = apply_update(P, c0 + dc, G.inst, sa, G.Wn, ROE ? A.wc : wu, dd);
         }
-    } else if constexpr (FWD) {
-        // for the backward sweep: a pair of values from each lane of the quad
+    } else if constexpr (FWD || KIND == GRP_BWD_REC) {
+        // for the backward sweep, or for k_update: a pair of values from each
+        // lane of the quad.  (A cell's record is read by its own quad only,
+        // before this; what lanes without a cell read of it is not used.)
         using T2 = std::conditional_t<std::is_same_v<T, double>, double2, float2>;
         T2 v;
         v.x = q < 2 ? (q == 0 ? d[0] : d[2]) : (q == 2 ? d[4] : Ds.v);
@@ -2671,6 +2674,34 @@ __global__ __launch_bounds__(64 * (ROE ? GRP_WAVES_ROE : GRP_WAVES)) void k_swee
     else
         e = group_sweep<T, KIND, false, ROE>(P, ip, G, wave);
     if (KIND == GRP_BWD_UPDATE) slot_update<false>(P.slot, SL_E40, G.inst, e);
+}
+
+// W^{n+1} = W^n + dW (Eq.17, Eq.40) of every cell from the records that the
+// last backward group sweep left.  Taken where a group has many chunks in a
+// wavefront (split_update in the host's sweep_groups): there the sweep is bound
+// by the instructions and the masked stores of one CU, and the update, which
+// uses one lane of a quad, by both.
+template <typename T, bool ONE>
+__global__ __launch_bounds__(256) void k_update(Params<T> P)
+{
+    const int c = xcd_block() * blockDim.x + threadIdx.x, N = P.nc;
+    int inst = -1;
+    double e = 0.0;
+    if (c < N) {
+        inst = live_inst<ONE>(P, P.cinst, c);
+        if (inst >= 0) {
+            using T2 = std::conditional_t<std::is_same_v<T, double>, double2, float2>;
+            const T2 *rec = reinterpret_cast<const T2 *>(P.srec + CR_STRIDE * (size_t)c);
+            const T2 r0 = rec[0], r1 = rec[1], r2 = rec[2];
+            const double *W = cur_state(P, inst);
+            double w[5], d[5] = {double(r0.x), double(r0.y), double(r1.x), double(r1.y), double(r2.x)};
+#pragma unroll
+            for (int k = 0; k < 5; k++) w[k] = W[k * N + c];
+            if (no_step(P.is[inst].cfl)) d[0] = d[1] = d[2] = d[3] = d[4] = 0.0;
+            e = apply_update(P, c, inst, P.ip[inst].sa, next_state(P, inst), w, d);
+        }
+    }
+    slot_update<false>(P.slot, SL_E40, inst, e);
 }
 
 // exact distance from each centroid to the nearest wall segment of its instance
@@ -2818,7 +2849,10 @@ template <typename T>
 void launch_sweep_grp(const Launch &L, const Params<T> &P, const SweepGroups &G, bool fwd, bool update)
 {
     if (G.n <= 0) return;
-    if (!fwd && update) launch_grp<T, GRP_BWD_UPDATE>(L, P, G);
+    if (!fwd && update && G.split_update) {
+        launch_grp<T, GRP_BWD_REC>(L, P, G);
+        LAUNCH_ONE(k_update, T, dim3(nblk(P.nc, L.block[3])), dim3(L.block[3]), P);
+    } else if (!fwd && update) launch_grp<T, GRP_BWD_UPDATE>(L, P, G);
     else if (!fwd) launch_grp<T, GRP_BWD>(L, P, G);
     else if (P.dWx) launch_grp<T, GRP_FWD2>(L, P, G);
     else launch_grp<T, GRP_FWD>(L, P, G);

@@ -24,6 +24,7 @@ def kernel_class(name: str):
              ("k_reduce", "reduce"), ("k_commit", "commit"),
              ("k_sweep_grp<double, 0", "sweep_fwd"), ("k_sweep_grp<double, 1", "sweep_fwd"),
              ("k_sweep_grp<double, 2", "sweep_bwd"), ("k_sweep_grp<double, 3", "sweep_bwd"),
+             ("k_sweep_grp<double, 4", "sweep_bwd"), ("k_sweep_grp<float, 4", "sweep_bwd"), ("k_update", "update"),
              ("k_sweep_grp<float, 0", "sweep_fwd"), ("k_sweep_grp<float, 1", "sweep_fwd"),
              ("k_sweep_grp<float, 2", "sweep_bwd"), ("k_sweep_grp<float, 3", "sweep_bwd"),
              ("k_sweep_wg<double, true", "sweep_fwd"), ("k_sweep_wg<double, false", "sweep_bwd"),
