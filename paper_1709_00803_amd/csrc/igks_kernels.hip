@@ -3,20 +3,29 @@
 //
 // One iteration = prep (per cell) -> flux (per face; each wave first takes
 // the Eq.23 time step of its instance from the prep minima) -> gather (per
-// cell) -> norm partial sums -> reduce (per instance: norms, Eq.25 CFL) ->
-// forward sweep (one launch per wavefront) -> backward sweep with the state
-// update -> commit (per instance).  No kernel waits on another inside a
-// launch: ordering comes from launch boundaries only (device-scope fences
-// inside a kernel would write back the XCD's whole L2).
+// cell) -> reduce (norm partial sums; per instance the Eq.25 CFL, and the
+// commit of the iteration before) -> the LU-SGS sweeps with the state update.
+// The last iteration of a chunk is committed by a launch of its own (every
+// iteration where the limiter may freeze).  The sweeps take either one launch
+// per wavefront (k_sweep), or one launch forward and one backward in which a
+// workgroup sweeps a whole group of cells, a sweep block or an instance
+// (k_sweep_grp), with the update in the backward one or after it (k_update).
+//
+// No workgroup waits for another: ordering between them comes from launch
+// boundaries only (device-scope fences inside a kernel would write back the
+// XCD's whole L2).  Inside a workgroup of k_sweep_grp the waves wait for each
+// other through a count in LDS.
 //
 // Data are structure-of-arrays in the library's internal cell order
 // (wavefront, then instance, then upload index) and face order (interior
 // faces, then boundary faces, each by their owner cell's position in the
-// spatial-tile order of the cell kernels).  Face results go to per-face arrays and every cell sums its faces
-// in a fixed order, so results are deterministic without floating-point
-// atomics; the only atomics are integer min/max on the bit patterns of
-// non-negative doubles.  Several independent instances (meshes and flow
-// conditions) share every launch; each cell and face carries its instance.
+// spatial-tile order of the cell kernels); what the gather and the sweeps read
+// of a face or a cell together is one 64-byte record (frec, crec, srec).
+// Every cell sums its faces in a fixed order, so results are deterministic
+// without floating-point atomics; the only atomics on memory are integer
+// min/max on the bit patterns of non-negative doubles, and a flag.  Several
+// independent instances (meshes and flow conditions) share every launch; each
+// cell and face carries its instance.
 #include "igks_dev.h"
 
 #include <math.h>
@@ -38,12 +47,6 @@ __device__ __forceinline__ double frcp(double b)
     x = fma(e, x, x);
     e = fma(-b, x, 1.0);
     return fma(e, x, x);
-}
-// a/b (b positive, finite) from frcp with one residual correction
-__device__ __forceinline__ double fdiv(double a, double b)
-{
-    const double x = frcp(b), q = a * x;
-    return fma(fma(-b, q, a), x, q);
 }
 // 1/sqrt(a) for a positive finite a: the hardware estimate refined by two
 // Newton steps of y <- y + y (1 - a y^2) / 2
@@ -376,12 +379,6 @@ __device__ __forceinline__ int live_inst(const Params<T> &P, const int *idx, int
     const InstScalars &s = P.is[inst];
     return (s.halt | (P.pend & s.bad)) ? -1 : inst;
 }
-template <typename T>
-__device__ __forceinline__ int face_inst(const Params<T> &P, int f)
-{
-    return P.ninst == 1 ? 0 : P.finst[f];
-}
-
 // The current state: the buffer ncommit points to, or, while the commit of
 // the iteration before is pending (P.pend), the one it will point to.
 template <typename T>
@@ -2153,28 +2150,31 @@ __global__ __launch_bounds__(256, ROE || !ONE ? 1 : 5) void k_sweep(Params<T> P,
 //
 // Measured (forward + backward sweep with the update, us), against a wave per
 // block that loaded everything in its turn: 64x32 plate in blocks of 128,
-// 92 -> 31; turbulent plate (100 wavefronts a block) 388 -> 83; 41k aerofoil
-// in blocks of 256, FP32, 119 -> 42; 250k aerofoil, two passes, 745 -> 178;
+// 92 -> 30; turbulent plate (100 wavefronts a block) 388 -> 82; 41k aerofoil
+// in blocks of 256, FP32, 119 -> 42; 250k aerofoil, two passes, 745 -> 172;
 // against one workgroup with a barrier after each wavefront: the polygon
-// cavity in its own order (385 wavefronts) 1940 -> 398.  Where wavefronts are
+// cavity in its own order (385 wavefronts) 1940 -> 368.  Where wavefronts are
 // single chunks the chain bounds it, 0.35 us a wavefront: its instructions
 // (about 70 FP64 and lane moves at 4 or more cycles) are half and its two LDS
 // trips most of the rest.  The ghosts' terms of the backward sweep are formed
 // ahead of the turn (turbulent plate, backward 62 -> 54 us with four waves),
 // and the state that the update needs is loaded there and not with the
-// chunk's other data, so that nothing spills (16 spilled registers: 64 us).  Where several groups share a CU or
-// wavefronts have several chunks the CU's memory pipe does (its data unit was
-// 90 % busy on the polygon cavity, at about 20 cache lines an instruction), so
-// a cell's residual and diagonal are one 64-byte record that the quad reads
-// with one instruction, the forward sweep leaves the backward one a record of
-// its own (increment, reciprocal diagonals), slots ride in the entries' flags
-// and chunk table, and entries without a term load the cell's own lines
-// (250k aerofoil 246 -> 186 us, 983k cells in colour order, forward 59 -> 48
-// us; the gather, which writes the records, 97 -> 102 us).
+// chunk's other data, so that nothing spills (16 spilled registers: 64 us).
+// Where several groups share a CU or wavefronts have several chunks the CU's
+// memory pipe does (its data unit was 90 % busy on the polygon cavity, at about
+// 20 cache lines an instruction), so a cell's residual and diagonal are one
+// 64-byte record that the quad reads with one instruction, the forward sweep
+// leaves the backward one a record of its own (increment, reciprocal
+// diagonals), slots ride in the entries' flags and chunk table, and entries
+// without a term load the cell's own lines (250k aerofoil 246 -> 186 us, 983k
+// cells in colour order, forward 59 -> 48 us; the gather, which writes the
+// records, 97 -> 102 us).  A branch around the coefficients of chunks that have
+// no terms (a sweep's first wavefront) cost the chain 3 to 5 % and gave nothing.
 //
 // The terms and their order are those of sweep_quad, so the iterates are
 // bitwise those of the launch-per-wavefront schedule.  The last backward sweep
-// also updates the state (Eq.17, Eq.40), after the chunk is counted.
+// also updates the state (Eq.17, Eq.40), after the chunk is counted, or, where
+// wavefronts are wide, leaves the increments in the cells' records for k_update.
 constexpr unsigned SPIN_LIMIT = 1u << 22;
 
 // sweep kinds of the group sweep: forward; forward of a second block pass
