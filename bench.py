@@ -87,11 +87,12 @@ class Progress:
             say(f"{self.label}: iteration {it}, drop {drop:.3e}")
 
 
-def kernel_bytes(n, f, e, sa, mixed):
+def kernel_bytes(n, f, e, sa, mixed, group=False):
     """Compulsory HBM bytes per iteration of each kernel class: every array
     element a kernel needs is counted once (re-reads of neighbour data are
     assumed to hit in cache); limiter off.  n cells, f faces, e cell-face
-    entries; sa: the SA equation is on."""
+    entries; sa: the SA equation is on; group: the sweeps of whole groups
+    (schedules 2 and 3) in place of a launch per wavefront."""
     d, i4 = 8, 4
     dw = 4 if mixed else 8
     s = 1 if sa else 0
@@ -105,16 +106,20 @@ def kernel_bytes(n, f, e, sa, mixed):
     # lam (+ SA sak) the sweeps read
     b["flux"] = (3 * i4 + 10 * d) * f + (5 + 8) * d * n + (8 + 1 + s) * d * f
     # cinst, cf_ptr, ipos; cf_face/cf_flag; flux, lam, length (+ SA: saf, sag,
-    # sak, normal); W (+ SA: nu, wall distance, vorticity, area); writes M,
-    # lsum, r2 (+ SA diagonal)
-    b["gather"] = 3 * i4 * n + 2 * i4 * e + 6 * d * f + 5 * d * n + (5 + 1 + 2) * d * n \
-        + s * (5 * d * f + 4 * d * n + d * n)
+    # sak, normal); W, lamc (+ SA: nu, wall distance, vorticity, area); writes
+    # the 64-byte cell record (M, lsum, SA diagonal, lamc) and r2
+    b["gather"] = 3 * i4 * n + 2 * i4 * e + 6 * d * f + (5 + 1) * d * n + (8 + 2) * d * n \
+        + s * (5 * d * f + 4 * d * n)
     b["reduce"] = 2 * d * n
     # cinst, cf_ptr; cf_nbr/cf_flag/cf_face; normal, length, lam (+ sak) of
-    # the faces swept; W, lamc, lsum (+ SA diagonal); writes dW
-    sweep = 2 * i4 * n + 3 * i4 * e + (4 + s) * d * f + (5 + 2 + s) * d * n + 5 * dw * n
-    b["sweep_fwd"] = sweep + 5 * d * n                      # + M
-    b["sweep_bwd"] = sweep + 5 * dw * n + 5 * d * n         # + own dW*, writes W^{n+1}
+    # the faces swept; W
+    sweep = 2 * i4 * n + 3 * i4 * e + (4 + s) * d * f + 5 * d * n
+    if group:
+        b["sweep_fwd"] = sweep + 8 * d * n + 8 * dw * n          # cell record; writes the forward record
+        b["sweep_bwd"] = sweep + 8 * dw * n + 5 * d * n          # that record; writes W^{n+1}
+    else:
+        b["sweep_fwd"] = sweep + 8 * d * n + 5 * dw * n          # cell record; writes dW
+        b["sweep_bwd"] = sweep + 8 * d * n + (5 + 5) * dw * n + 5 * d * n   # own dW* too; writes W^{n+1}
     return b
 
 
@@ -277,12 +282,12 @@ def measure(igks, meshes, flows, precision, args, schedule, label):
     run(solver, args.profile_iters, batched)
     kt = solver.kernel_times()      # ms per iteration, per kernel class
     solver.set_profiling(False)
+    sweep_wg = schedule[4] >= 2
     kb = {}
     for m, f, nf in zip(meshes, flows, nfs):
         e = int(np.sum(np.diff(m.cell_ptr)))
-        for k, v in kernel_bytes(m.n_cells, nf, e, f[3] >= 0, mixed).items():
+        for k, v in kernel_bytes(m.n_cells, nf, e, f[3] >= 0, mixed, sweep_wg).items():
             kb[k] = kb.get(k, 0) + v
-    sweep_wg = schedule[4] == 2
     if not sweep_wg and solver.nlev > 1:
         # one launch per wavefront: the forward class covers wavefronts
         # 1 .. nlev-1 (the first wavefront's forward increments are formed
@@ -306,7 +311,7 @@ def roofline_of(args, solver, kt, kb, out, mixed):
     faces = solver.total_faces
     schedule = out["schedule"]
     dom = max(kt, key=lambda k: kt[k])
-    sweep_wg = schedule[4] == 2
+    sweep_wg = schedule[4] >= 2
     launches = {"sweep_fwd": 1 if sweep_wg else max(solver.nlev - 1, 1),
                 "sweep_bwd": 1 if sweep_wg else max(solver.nlev - 1, 1)}.get(dom, 1)
     launch_ms = kt[dom] / launches
@@ -346,7 +351,7 @@ def roofline_of(args, solver, kt, kb, out, mixed):
 
 # sweep blocks (cells, coupled_blocks) of the small time-to-solution workloads:
 # the smallest that kept the iteration count (block sizes of 64-1024
-# measured on each; a wave sweeps each block, all blocks at once)
+# measured on each; a workgroup sweeps each block, all blocks at once)
 SMALL_BLOCKS = 128
 
 
@@ -436,7 +441,7 @@ def time_to_drop_joukowski(igks, mg):
     """The 40k-cell laminar Joukowski (Ma 0.5, Re 5000, alpha 2) from the
     impulsive start to a 1e-10 drop: block LU-SGS (blocks of at most 256
     cells grown along the strongest couplings, generation order inside, a
-    wave per block) in FP64 and mixed precision, against the colour order
+    workgroup per block) in FP64 and mixed precision, against the colour order
     (3 wavefronts, fast sweeps that do not converge) and the explicit
     scheme."""
     flow = WORKLOADS["jouk40k"]["flow"]
