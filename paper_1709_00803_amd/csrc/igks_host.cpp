@@ -1168,7 +1168,6 @@ int copy_out(igks_ctx *c, int inst, size_t sk, size_t sc, const double *src, dou
     // Pieces t, t + threads, ... through the slots of thread t: `depth` of
     // them are queued ahead of the one that is copied out.
     auto work = [&](int t) {
-        if (t > 0 && hipSetDevice(c->dev) != hipSuccess) { err = (int)hipErrorInvalidDevice; return; }
         auto queue = [&](int j) {
             const int p = t + j * threads, u0 = p * STAGE_CELLS, m = std::min(STAGE_CELLS, n - u0);
             if (p >= pieces) return;
@@ -1192,9 +1191,13 @@ int copy_out(igks_ctx *c, int inst, size_t sk, size_t sc, const double *src, dou
     std::thread th[STAGE_THREADS];
     int started = 1;
     try {
-        for (; started < threads; started++) th[started] = std::thread(work, started);
+        for (; started < threads; started++)
+            th[started] = std::thread([&](int t) {
+                if (hipSetDevice(c->dev) == hipSuccess) work(t);
+                else err = (int)hipErrorInvalidDevice;
+            }, started);
     } catch (...) {
-        // no more threads: their pieces are done below
+        // no more threads: their pieces are done below, on the caller's device
     }
     work(0);
     for (int t = 1; t < started; t++) th[t].join();
