@@ -711,7 +711,9 @@ __device__ __forceinline__ float inv_cfl(float cfl) { return 1.0f / cfl; }
 // A CFL number of 0, or one so small that Lambda_c / CFL overflows, makes no
 // step: the update takes 0 for whatever the sweeps made of the infinite
 // diagonal.  (Mending the reciprocals of the diagonals instead took k_sweep on
-// 983k cells from 48 + 82 to 52 + 85 us; this, where it stands, takes nothing.)
+// 983k cells from 48 + 82 to 52 + 85 us; this, where it stands, takes nothing.
+// FP32 divides, which gives 0 by itself; asked there too, two registers more
+// took a wave from the SIMDs, backward on 64 instances 134 -> 143 us.)
 __device__ __forceinline__ bool no_step(double cfl) { return fabs(cfl) < 1e-300; }
 // Omega / dt_imp = Lambda_c / CFL (Eq.24), icfl = 1 / CFL used in FP64 only
 // (a product of its own, never fused into the diagonal's sum)
@@ -2077,7 +2079,7 @@ __device__ __forceinline__ double sweep_quad(const Params<T> &P, int c, int q, i
     if (ovf >= 0)
         upper(P.cf_face[MAXV * ovf + q], MAXV * ovf + q, P.cf_nbr[MAXV * ovf + q], P.cf_flag[MAXV * ovf + q]);
     if (q != 0) return 0.0;
-    if (no_step(sc.cfl)) {
+    if ((std::is_same_v<T, double> || ROE) && no_step(sc.cfl)) {
         const double none[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
         return apply_update(P, c, inst, ip.sa, next_state(P, inst), w, none);
     }
@@ -2160,9 +2162,10 @@ __global__ __launch_bounds__(256, ROE || !ONE ? 1 : 5) void k_sweep(Params<T> P,
 // ahead of the turn (turbulent plate, backward 62 -> 54 us with four waves),
 // and the state that the update needs is loaded there and not with the
 // chunk's other data, so that nothing spills (16 spilled registers: 64 us).
-// Where several groups share a CU or wavefronts have several chunks the CU's
-// memory pipe does (its data unit was 90 % busy on the polygon cavity, at about
-// 20 cache lines an instruction), so a cell's residual and diagonal are one
+// Where wavefronts have several chunks the CU's memory pipe does (its data unit
+// is 90 % busy on the polygon cavity, at 21 to 23 cache lines an instruction;
+// 44 to 56 % where two groups share a CU, on the 250k aerofoil, whose waves wait
+// 30 to 47 % of their time), so a cell's residual and diagonal are one
 // 64-byte record that the quad reads with one instruction, the forward sweep
 // leaves the backward one a record of its own (increment, reciprocal
 // diagonals), slots ride in the entries' flags and chunk table, and entries
@@ -2680,7 +2683,8 @@ __global__ __launch_bounds__(64 * (ROE ? GRP_WAVES_ROE : GRP_WAVES)) void k_swee
 // last backward group sweep left.  Taken where a group has many chunks in a
 // wavefront (split_update in the host's sweep_groups): there the sweep is bound
 // by the instructions and the masked stores of one CU, and the update, which
-// uses one lane of a quad, by both.
+// uses one lane of a quad, by both.  Here it streams 144 bytes a cell: 4.8 us on
+// 9k cells (a launch), 20 us on 750k (5.5 TB/s).
 template <typename T, bool ONE>
 __global__ __launch_bounds__(256) void k_update(Params<T> P)
 {
