@@ -595,7 +595,7 @@ void sweep_groups(igks_ctx *ctx, const std::vector<int> &order, const std::vecto
     // update between its turns, and where their wavefronts are wider than a
     // chunk twelve (three per SIMD, what the registers hold; eight with the Roe
     // operator), which run side by side.  Forward + backward sweep in us with
-    // 4 / 8 / 12 waves: 64x32 plate, 21 blocks 33 / 30 / 32; turbulent plate, 60
+    // 4 / 8 / 12 waves: 64x32 plate, 21 blocks 33 / 30 / 32; turbulent plate, 89
     // blocks 92 / 82 / 82; 250k aerofoil, 523 blocks of 1.8 chunks a wavefront
     // 172 / 194 / 201; in natural order the plate 125 / 98 / 93, the polygon
     // cavity 609 / 413 / 368, the 100x100 cavity (3.6 chunks a wavefront) 431 /
